@@ -165,9 +165,20 @@ __device__ __forceinline__ i8_t ld_op6(const uint8_t* rec, int lane) {
   return r;
 }
 
-__device__ __forceinline__ f16v_t mfma6(const i8_t& A, const i8_t& B, const f16v_t& C) {
-  // FP6 E2M3 x FP6 E2M3, unit E8M0 scales (127 = 2^0).
-  return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(A, B, C, 2, 2, 0, 127, 0, 127);
+// Column sums of an FP6 E2M3 operand: the MFMA against an all-ones A operand.
+// The ones are FP4 E2M1 (1.0 = 0b0010; four registers where FP6 takes six,
+// at the same rate) and are written here each time: four moves per block cost
+// less than registers held through the block, where they were spilled.
+__device__ __forceinline__ f16v_t mfma_ones(const i8_t& B) {
+  i8_t ones = {};
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    int w;
+    asm volatile("v_mov_b32 %0, 0x22222222" : "=v"(w));
+    ones[i] = w;
+  }
+  const f16v_t zero = {};
+  return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(ones, B, zero, 4, 2, 0, 127, 0, 127);
 }
 
 __device__ __forceinline__ half_t hmax(half_t a, half_t b) { return a > b ? a : b; }
@@ -243,25 +254,26 @@ __device__ __forceinline__ void exp2_h2x4(const h2_t x[4], h2_t y[4]) {
       : "v"(x[0]), "v"(x[1]), "v"(x[2]), "v"(x[3]));
 }
 
-// Packed maximum of 16 pairs (a tree of 15 v_pk_max_f16 in one block).
+// fp32 value of the fp16 exponential of the low half of x.
+__device__ __forceinline__ float exp2_low(h2_t x) {
+  h2_t y;
+  asm("v_exp_f16 %0, %1\n\ts_nop 0" : "=v"(y) : "v"(x));
+  return (float)y[0];
+}
+
+// Packed maximum of 16 pairs: seven three-operand maxima and one of two
+// (against fifteen of two operands).  The inputs are finite or -inf.
 __device__ __forceinline__ h2_t hmax16(const h2_t x[16]) {
-  h2_t y, a1, a2, a3, a4, a5, a6, a7;
-  asm("v_pk_max_f16 %0, %8, %9\n\t"
-      "v_pk_max_f16 %1, %10, %11\n\t"
-      "v_pk_max_f16 %2, %12, %13\n\t"
-      "v_pk_max_f16 %3, %14, %15\n\t"
-      "v_pk_max_f16 %4, %16, %17\n\t"
-      "v_pk_max_f16 %5, %18, %19\n\t"
-      "v_pk_max_f16 %6, %20, %21\n\t"
-      "v_pk_max_f16 %7, %22, %23\n\t"
-      "v_pk_max_f16 %0, %0, %1\n\t"
-      "v_pk_max_f16 %2, %2, %3\n\t"
-      "v_pk_max_f16 %4, %4, %5\n\t"
-      "v_pk_max_f16 %6, %6, %7\n\t"
-      "v_pk_max_f16 %0, %0, %2\n\t"
-      "v_pk_max_f16 %4, %4, %6\n\t"
-      "v_pk_max_f16 %0, %0, %4"
-      : "=&v"(y), "=&v"(a1), "=&v"(a2), "=&v"(a3), "=&v"(a4), "=&v"(a5), "=&v"(a6), "=&v"(a7)
+  h2_t y, a1, a2, a3, a4;
+  asm("v_pk_maximum3_f16 %0, %5, %6, %7\n\t"
+      "v_pk_maximum3_f16 %1, %8, %9, %10\n\t"
+      "v_pk_maximum3_f16 %2, %11, %12, %13\n\t"
+      "v_pk_maximum3_f16 %3, %14, %15, %16\n\t"
+      "v_pk_maximum3_f16 %4, %17, %18, %19\n\t"
+      "v_pk_maximum3_f16 %0, %0, %1, %20\n\t"
+      "v_pk_maximum3_f16 %2, %2, %3, %4\n\t"
+      "v_pk_max_f16 %0, %0, %2"
+      : "=&v"(y), "=&v"(a1), "=&v"(a2), "=&v"(a3), "=&v"(a4)
       : "v"(x[0]), "v"(x[1]), "v"(x[2]), "v"(x[3]), "v"(x[4]), "v"(x[5]), "v"(x[6]), "v"(x[7]), "v"(x[8]),
         "v"(x[9]), "v"(x[10]), "v"(x[11]), "v"(x[12]), "v"(x[13]), "v"(x[14]), "v"(x[15]));
   return y;
@@ -353,7 +365,7 @@ __device__ __forceinline__ void quantize_q_half_group(const h2_t (&x)[16], i8_t&
 template <int G>
 struct Hif4State {
   f16v_t O[2 * G];
-  half_t m_run;
+  h2_t m_run;       // running maximum, in both halves
   float l_star;     // l / rho (consistent or mismatched per NORM)
   float inv_rho;    // 1 / rho
 };
@@ -361,7 +373,7 @@ struct Hif4State {
 template <int G, int NORM, bool DEBUG, bool QMEAN, bool MASK>
 __device__ __forceinline__ void hif4_block(const AttnArgs& a, const TileMap& tm, const uint8_t* cur, int J, int lane,
                                            int h, int col, int qi, bool row_ok, const i8_t (&qop)[G],
-                                           const float (&wq)[G], float cmu, const i8_t& ones, Hif4State<G>& st,
+                                           const float (&wq)[G], float cmu, Hif4State<G>& st,
                                            const ChunkStream& cs) {
   constexpr int DT = 2 * G;
   constexpr ChunkLayout lay = chunk_layout_hif4(G, QMEAN);
@@ -417,6 +429,7 @@ __device__ __forceinline__ void hif4_block(const AttnArgs& a, const TileMap& tm,
     }
 #pragma unroll
     for (int v2 = 0; v2 < 8; ++v2) s2[t][v2] = pack2_f16(sacc[2 * v2], sacc[2 * v2 + 1]);
+    if (t == 0) __builtin_amdgcn_sched_barrier(0);
   }
   if (MASK) {
     const half_t ninf = (half_t)(-__builtin_inff());
@@ -429,8 +442,7 @@ __device__ __forceinline__ void hif4_block(const AttnArgs& a, const TileMap& tm,
   // ---- running max (FP16), exchanged with lane l^32.
   h2_t mx2 = hmax16(&s2[0][0]);
   mx2 = hmax_halves(max_with_partner(mx2));            // block row max, both halves
-  const h2_t mr2 = {st.m_run, st.m_run};
-  const h2_t mn2 = hmax2(mr2, mx2);                    // m_new, both halves
+  const h2_t mn2 = hmax2(st.m_run, mx2);               // m_new, both halves
   stream_piece<CB>(cs, 4);
   // ---- P = 2^(S2 - m_new); r = 2^(m - m_new) and the block max A = 2^(mx - m_new).
   h2_t p2[2][8];
@@ -443,10 +455,9 @@ __device__ __forceinline__ void hif4_block(const AttnArgs& a, const TileMap& tm,
       for (int i = 0; i < 4; ++i) xin[i] = s2[t][4 * q + i] - mn2;
       exp2_h2x4(xin, &p2[t][4 * q]);
     }
-  const h2_t ra = exp2_h2(h2_t{mr2[0], mx2[0]} - mn2);
-  const float r = (float)ra[0];
-  const float A = (float)ra[1];
-  st.m_run = mn2[0];
+  const float r = exp2_low(st.m_run - mn2);
+  const float A = exp2_low(mx2 - mn2);
+  st.m_run = mn2;
 
   float psum = 0.0f;
   if (NORM == 1) {
@@ -468,7 +479,7 @@ __device__ __forceinline__ void hif4_block(const AttnArgs& a, const TileMap& tm,
   }
   const PQuant pq = quantize_p_block<DEBUG>(p2, A, lane, h, dcodes, dmeta);
   const float bval = pq.bval;
-  const i6_t pk = __builtin_amdgcn_cvt_scalef32_pk32_fp6_f16(pq.ov, 1.0f);
+  const i6_t pk = __builtin_amdgcn_cvt_scalef32_pk32_fp6_f16(pq.ov, kPScale);
   i8_t pop;
 #pragma unroll
   for (int i = 0; i < 6; ++i) pop[i] = pk[i];
@@ -476,24 +487,27 @@ __device__ __forceinline__ void hif4_block(const AttnArgs& a, const TileMap& tm,
   pop[7] = 0;
 
   stream_piece<CB>(cs, 6);
-  // ---- deferred rescale bookkeeping (lane-uniform factors).
-  if (__builtin_expect(J > 0 && __builtin_amdgcn_ballot_w64(r == 0.0f) != 0, 0)) {
-    // history wiped for some rows: O <- 0*O, l <- 0*l there
+  // ---- deferred rescale bookkeeping (lane-uniform factors), in the blocks
+  // where the running maximum of some row of the wave moved.
+  if (__builtin_amdgcn_ballot_w64(r != 1.0f) != 0) {
+    if (__builtin_expect(J > 0 && __builtin_amdgcn_ballot_w64(r == 0.0f) != 0, 0)) {
+      // history wiped for some rows: O <- 0*O, l <- 0*l there
 #pragma unroll
-    for (int dt = 0; dt < DT; ++dt)
+      for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) st.O[dt][v] = r == 0.0f ? 0.0f : st.O[dt][v];
-    st.l_star = r == 0.0f ? 0.0f : st.l_star;
-  }
-  st.inv_rho = (r == 0.0f) ? 1.0f : st.inv_rho * __builtin_amdgcn_rcpf(r);
-  if (__builtin_expect(__builtin_amdgcn_ballot_w64(st.inv_rho > 0x1p64f) != 0, 0)) {
-    const float rho = __builtin_amdgcn_rcpf(st.inv_rho);
+        for (int v = 0; v < 16; ++v) st.O[dt][v] = r == 0.0f ? 0.0f : st.O[dt][v];
+      st.l_star = r == 0.0f ? 0.0f : st.l_star;
+    }
+    st.inv_rho = (r == 0.0f) ? 1.0f : st.inv_rho * __builtin_amdgcn_rcpf(r);
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(st.inv_rho > 0x1p64f) != 0, 0)) {
+      const float rho = __builtin_amdgcn_rcpf(st.inv_rho);
 #pragma unroll
-    for (int dt = 0; dt < DT; ++dt)
+      for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) st.O[dt][v] *= rho;
-    st.l_star *= rho;
-    st.inv_rho = 1.0f;
+        for (int v = 0; v < 16; ++v) st.O[dt][v] *= rho;
+      st.l_star *= rho;
+      st.inv_rho = 1.0f;
+    }
   }
   const float wp = 0.25f * bval * st.inv_rho;      // b_P/4 / rho
   // ---- [O | l] += P^ [V^ | 1]; each V^ group enters two MFMAs (split base),
@@ -521,8 +535,7 @@ __device__ __forceinline__ void hif4_block(const AttnArgs& a, const TileMap& tm,
   if (NORM == 1) {
     st.l_star = __builtin_fmaf(psum, st.inv_rho, st.l_star);
   } else {
-    const f16v_t zero = {};
-    const f16v_t lacc = mfma6(ones, pop, zero);
+    const f16v_t lacc = mfma_ones(pop);
     st.l_star = __builtin_fmaf(lacc[0], wp, st.l_star);
   }
 }
@@ -565,27 +578,12 @@ __global__ void __launch_bounds__(256, (G == 1 ? 4 : (G == 2 ? 3 : 1))) k_attn_h
 #pragma unroll
   for (int g = 0; g < G; ++g) quantize_q_half_group(xs[g], qop[g], wq[g]);
 
-  i8_t ones;
-  {
-    uint32_t w[6] = {0, 0, 0, 0, 0, 0};
-#pragma unroll
-    for (int s = 0; s < 32; ++s) {
-      const int bit = 6 * s;
-      w[bit >> 5] |= kE2M3One << (bit & 31);
-      if ((bit & 31) > 26) w[(bit >> 5) + 1] |= kE2M3One >> (32 - (bit & 31));
-    }
-#pragma unroll
-    for (int i = 0; i < 6; ++i) ones[i] = (int)w[i];
-    ones[6] = 0;
-    ones[7] = 0;
-  }
-
   Hif4State<G> st;
 #pragma unroll
   for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
     for (int v = 0; v < 16; ++v) st.O[dt][v] = 0.0f;
-  st.m_run = (half_t)(-__builtin_inff());
+  st.m_run = h2_t{(half_t)(-__builtin_inff()), (half_t)(-__builtin_inff())};
   st.l_star = 0.0f;
   st.inv_rho = 1.0f;
 
@@ -599,9 +597,9 @@ __global__ void __launch_bounds__(256, (G == 1 ? 4 : (G == 2 ? 3 : 1))) k_attn_h
     const ChunkStream cs{smem + ((J + 1) & 1) * cbytes, ws_base + (size_t)(J + 1 < tm.nJ ? J + 1 : J) * cbytes,
                          wave_u};
     if (J < jw_last)
-      hif4_block<G, NORM, DEBUG, QMEAN, false>(a, tm, cur, J, lane, h, col, qi, row_ok, qop, wq, cmu, ones, st, cs);
+      hif4_block<G, NORM, DEBUG, QMEAN, false>(a, tm, cur, J, lane, h, col, qi, row_ok, qop, wq, cmu, st, cs);
     else if (J == jw_last)
-      hif4_block<G, NORM, DEBUG, QMEAN, true>(a, tm, cur, J, lane, h, col, qi, row_ok, qop, wq, cmu, ones, st, cs);
+      hif4_block<G, NORM, DEBUG, QMEAN, true>(a, tm, cur, J, lane, h, col, qi, row_ok, qop, wq, cmu, st, cs);
     else
       stream_pieces_from<cbytes>(cs, 0);
     wait_async_copies();
@@ -624,7 +622,7 @@ __global__ void __launch_bounds__(256, (G == 1 ? 4 : (G == 2 ? 3 : 1))) k_attn_h
       }
     if (h == 0)
       a.lse[(size_t)tm.hq * a.total_tokens + tm.t0 + qi] =
-          (float)st.m_run * 0.69314718055994531f + logf(st.l_star) - logf(st.inv_rho);
+          (float)st.m_run[0] * 0.69314718055994531f + logf(st.l_star) - logf(st.inv_rho);
   }
 }
 
@@ -920,7 +918,7 @@ __global__ void __launch_bounds__(256, (D <= 128 ? 2 : 1)) k_attn_ponly(AttnArgs
         l_star *= rho;
         inv_rho = 1.0f;
       }
-      const float wp = 0.25f * pq.bval * inv_rho;
+      const float wp = (0.25f / kPScale) * pq.bval * inv_rho;
       // B operand chunks of the 32x32x16 MFMA: c = 2t + jp holds the values of
       // p2[t][4jp .. 4jp+3], i.e. operand slots 16t + 8jp + [0, 8)
       h8_t pb[4];

@@ -30,26 +30,26 @@ typedef float f16v_t __attribute__((ext_vector_type(16)));
 typedef int i6_t __attribute__((ext_vector_type(6)));
 typedef int i8_t __attribute__((ext_vector_type(8)));
 
-// FP6 E2M3 encoding of 1.0 (sign 0, exponent 01, mantissa 000), replicated
-// in 6-bit fields: the all-ones operand of the fused normalizer [V^ | 1].
-constexpr uint32_t kE2M3One = 0x08;
 
 
-// Smallest E6M2 byte whose value b satisfies 1.75*b >= A (A >= 0, an fp16 or
-// fp16-softmax value held exactly in fp32), without branches.  Write
-// A = s*2^E with s in [1,2).  The values 1.75*b of the bases near A are
-// 1.09375, 1.3125, 1.53125 (mantissas m = 1, 2, 3, exponent E-1), 1.75 and
-// 2.1875 (m = 0, 1, exponent E) times 2^E, so the smallest covering base is
-// code 4(E+30) + 1 + [s > 1.09375] + [s > 1.3125] + [s > 1.53125] + [s > 1.75];
-// the comparisons are exact on the fp32 significand bits.  A = 0 gives 0.
-__device__ __forceinline__ uint32_t e6m2_ceil(float A) {
-  const uint32_t bits = __float_as_uint(A);
-  const uint32_t mant = bits & 0x7FFFFFu;
-  const int c = (int)(mant > 0xC0000u) + (int)(mant > 0x280000u) + (int)(mant > 0x440000u) +
-                (int)(mant > 0x600000u);
-  const int code = 4 * (int)(bits >> 23) - 387 + c;
-  return A > 0.0f ? (uint32_t)code : 0u;
+// fp32 bits of the smallest E6M2 value b with 1.75*b >= A (A >= 0, an fp16 or
+// fp16-softmax value held exactly in fp32); A = 0 gives 0.  b is A/1.75 rounded
+// up to two mantissa bits.  The product with 4/7 (1 - 2^-20) stands for the
+// quotient: where A = 1.75 b exactly it lies just below b and rounds up to b;
+// any other fp16 A lies at least 2^-12 (relative) from such a value, far more
+// than the bias and the rounding of the product, so it rounds up to the same
+// value as the quotient.  Three instructions against the fourteen of counting
+// significand thresholds.
+__device__ __forceinline__ uint32_t e6m2_cover_bits(float A) {
+  const float y = A * 0x1.249236p-1f;                  // 4/7 (1 - 2^-20)
+  return (__float_as_uint(y) + 0x1FFFFFu) & 0xFFE00000u;
 }
+
+// E6M2 byte of the value with fp32 bits b (0 for b = 0).
+__device__ __forceinline__ uint32_t e6m2_code_of(uint32_t b) { return b ? (b - 0x30000000u) >> 21 : 0u; }
+
+// Smallest E6M2 byte whose value b satisfies 1.75*b >= A; A = 0 gives 0.
+__device__ __forceinline__ uint32_t e6m2_ceil(float A) { return e6m2_code_of(e6m2_cover_bits(A)); }
 
 // E6M2 value b = (1 + m/4) * 2^(e-31) of byte e<<2|m, built from its bits.
 __device__ __forceinline__ float e6m2_bits_value(uint32_t code) {
