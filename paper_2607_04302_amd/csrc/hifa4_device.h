@@ -30,8 +30,6 @@ typedef float f16v_t __attribute__((ext_vector_type(16)));
 typedef int i6_t __attribute__((ext_vector_type(6)));
 typedef int i8_t __attribute__((ext_vector_type(8)));
 
-
-
 // fp32 bits of the smallest E6M2 value b with 1.75*b >= A (A >= 0, an fp16 or
 // fp16-softmax value held exactly in fp32); A = 0 gives 0.  b is A/1.75 rounded
 // up to two mantissa bits.  The product with 4/7 (1 - 2^-20) stands for the
@@ -83,11 +81,6 @@ __device__ __forceinline__ float round_const(int sh) {
   return sh == 0 ? 12582912.0f : (sh == 1 ? 6291456.0f : 3145728.0f);
 }
 
-// o = u * 2^-sh for one element magnitude a (>= 0).
-__device__ __forceinline__ float hif4_elem(float a, float R, float C) {
-  return __builtin_fmaf(a, R, C) - C;
-}
-
 // fp16 softmax exponential E(x) = fp16(2^x) for a pair of fp16 x (x = -inf
 // gives 0): v_exp_f16 on the low half, then its SDWA form on the high half,
 // which keeps the low half of the destination.  The SDWA form reads the
@@ -104,14 +97,6 @@ __device__ __forceinline__ h2_t exp2_h2(h2_t x) {
   return y;
 }
 
-// fp16(a*b) for fp32 a and b, the exact product rounded once (v_fma_mix with
-// an fp16 destination rounds the fused result once; low half of the result).
-__device__ __forceinline__ half_t mul_rn16(float a, float b) {
-  half_t y;
-  asm("v_fma_mixlo_f16 %0, %1, %2, 0" : "=v"(y) : "v"(a), "v"(b));
-  return y;
-}
-
 // Pack fp16(fp32(a*c)) and fp16(fp32(b*c)): the products are rounded to fp32,
 // then converted to fp16 (round to nearest even) by one packed conversion.
 __device__ __forceinline__ h2_t scale2_to_f16(float a, float b, float c) {
@@ -125,13 +110,6 @@ __device__ __forceinline__ h2_t scale2_to_f16(float a, float b, float c) {
 __device__ __forceinline__ h2_t pack2_f16(float a, float b) {
   h2_t y;
   asm("v_cvt_pk_f16_f32 %0, %1, %2" : "=v"(y) : "v"(a), "v"(b));
-  return y;
-}
-
-// Pack fp16(a*c) and fp16(b*c) (each rounded once) into one register.
-__device__ __forceinline__ h2_t mul2_rn16(float a, float b, float c) {
-  h2_t y;
-  asm("v_fma_mixlo_f16 %0, %1, %3, 0\n\tv_fma_mixhi_f16 %0, %2, %3, 0" : "=&v"(y) : "v"(a), "v"(b), "v"(c));
   return y;
 }
 
@@ -155,93 +133,6 @@ __device__ __forceinline__ half_t div_rn16(float k, float s) {
   const bool above = r > 0.0f;                      // true quotient > q (s > 0)
   const bool nb_above = (float)nb > q;
   return (above == nb_above) ? nb : h;
-}
-
-// The same quotient from a reciprocal rs = RN32(1/s): k*rs = (k/s)(1 + d)
-// with |d| <= 2^-24, so q = RN32(k*rs) lies within 1.5 fp32 ulps of k/s and
-// RN16(q) = RN16(k/s) unless q's bits below the fp16 precision (the low 13
-// mantissa bits) are within 3 of the halfway pattern 0x1000, or q is in
-// fp16's subnormal range; those take div_rn16.
-__device__ __forceinline__ half_t div_rn16_rcp(float k, float s, float rs) {
-  const float q = k * rs;
-  const uint32_t b = __float_as_uint(q);
-  const bool near_mid = ((b & 0x1FFFu) - 0xFFDu) < 7u;
-  const bool tiny = (b & 0x7F800000u) < 0x38800000u && (b & 0x7FFFFFFFu) != 0u;
-  if (__builtin_expect(near_mid || tiny, 0)) return div_rn16(k, s);
-  return (half_t)q;
-}
-
-__device__ __forceinline__ float shfl_xor32(float v) {
-  return __shfl_xor(v, 32);
-}
-__device__ __forceinline__ uint32_t shfl_xor32_u(uint32_t v) {
-  return (uint32_t)__shfl_xor((int)v, 32);
-}
-
-// ---------------------------------------------------------------------------
-// Lane-split group quantization.  A 64-element group is held by a lane pair
-// (lane l and l^32), 32 elements each, as 8 complete 4-element blocks.
-// `q4[k]` is the global index (0..15) of the lane's k-th 4-block, and a4[k]
-// its maximum magnitude.  Both lanes compute identical group metadata.
-struct GroupMeta {
-  uint32_t base;    // E6M2 byte
-  uint32_t e2;      // 8 bits
-  uint32_t e3;      // 16 bits
-  float b;          // base value
-};
-
-// a4_all[0..15]: the maxima of all 16 4-blocks of the group, in block order.
-__device__ __forceinline__ GroupMeta group_meta(const float a4_all[16]) {
-  GroupMeta g;
-  float A8[8];
-#pragma unroll
-  for (int j = 0; j < 8; ++j) A8[j] = fmaxf(a4_all[2 * j], a4_all[2 * j + 1]);
-  float A = A8[0];
-#pragma unroll
-  for (int j = 1; j < 8; ++j) A = fmaxf(A, A8[j]);
-  g.base = e6m2_ceil(A);
-  g.b = e6m2_value(g.base);
-  const float half_range = 0.875f * g.b;
-  g.e2 = 0;
-#pragma unroll
-  for (int j = 0; j < 8; ++j) g.e2 |= (A8[j] <= half_range ? 1u : 0u) << j;
-  g.e3 = 0;
-#pragma unroll
-  for (int q = 0; q < 16; ++q) {
-    const float lim = ((g.e2 >> (q >> 1)) & 1u) ? 0.5f * half_range : half_range;
-    g.e3 |= (a4_all[q] <= lim ? 1u : 0u) << q;
-  }
-  return g;
-}
-
-__device__ __forceinline__ int block_shift(const GroupMeta& g, int q4) {
-  return (int)((g.e2 >> (q4 >> 1)) & 1u) + (int)((g.e3 >> q4) & 1u);
-}
-
-// Which 4-blocks a lane holds.  kRows: lane half h holds the contiguous
-// elements [32h, 32h+32), i.e. blocks 8h..8h+7 (Q, K along channels).
-// kKeys: the lane's k-th block is (t = k/4, j = k%4), elements
-// 32t + 8j + 4h + [0,4), i.e. block 8t + 2j + h (V along tokens, and P,
-// following the 32x32 MFMA output layout of S^T).
-enum { kRows = 0, kKeys = 1 };
-
-template <int LAYOUT>
-__device__ __forceinline__ int own_block(int k, int h) {
-  return LAYOUT == kRows ? 8 * h + k : 8 * (k >> 2) + 2 * (k & 3) + h;
-}
-
-// Assemble the 16 block maxima of the group from the lane's 8 and its
-// partner's (lane l^32) 8, with static register indexing.
-template <int LAYOUT>
-__device__ __forceinline__ void gather_a4(const float own[8], float all[16], int h) {
-#pragma unroll
-  for (int k = 0; k < 8; ++k) {
-    const float other = shfl_xor32(own[k]);
-    const int lo = LAYOUT == kRows ? k : 8 * (k >> 2) + 2 * (k & 3);
-    const int hi = LAYOUT == kRows ? 8 + k : lo + 1;
-    all[lo] = h ? other : own[k];
-    all[hi] = h ? own[k] : other;
-  }
 }
 
 }  // namespace hifa4

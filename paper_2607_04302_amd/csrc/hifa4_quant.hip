@@ -8,6 +8,8 @@
 #include "hifa4_internal.h"
 #include "hifa4_packed.h"
 
+#include <algorithm>
+
 namespace hifa4 {
 
 // Token index (row of the [T, H, D] view) of position i in sequence b.
@@ -20,147 +22,263 @@ __device__ __forceinline__ int seq_len(const int* cu, int b, int S) {
   return cu ? min(cu[b + 1] - cu[b], S) : S;
 }
 
-// Load 32 consecutive fp16 channels of one (token, head) row and apply the
-// Smooth-QK scale: q~ = fp16(q*s) and k~ = fp16(k/s), the exact product or
-// quotient rounded once.  Returns the values as fp32.
-// For K, `rs` may hold the reciprocals RN32(1/s) of the same 32 channels;
-// the quotient then comes from div_rn16_rcp (same result, mostly without a
-// division).
-template <bool kIsK>
-__device__ __forceinline__ void load_smoothed32(const half_t* __restrict__ src,
-                                                const float* __restrict__ s, float x[32],
-                                                const float* rs = nullptr) {
-  const uint4* p = reinterpret_cast<const uint4*>(src);
-#pragma unroll
-  for (int v = 0; v < 4; ++v) {
-    uint4 w = p[v];
-    const half_t* h = reinterpret_cast<const half_t*>(&w);
-#pragma unroll
-    for (int i = 0; i < 8; ++i) x[8 * v + i] = (float)h[i];
-  }
-  if (s) {
-    if (kIsK && rs) {
-#pragma unroll
-      for (int c = 0; c < 32; ++c) x[c] = (float)div_rn16_rcp(x[c], s[c], rs[c]);
-    } else {
-#pragma unroll
-      for (int c = 0; c < 32; ++c) x[c] = (float)(kIsK ? div_rn16(x[c], s[c]) : mul_rn16(x[c], s[c]));
-    }
-  }
+// Packed-fp16 pieces of the canonical quantizers.
+typedef unsigned short u16x2_t __attribute__((ext_vector_type(2)));
+
+__device__ __forceinline__ u16x2_t as_u16(h2_t x) { return __builtin_bit_cast(u16x2_t, x); }
+
+// Level-2 and level-3 decisions of both halves of a pair of 4-block maxima a4
+// whose 8-block maxima are a8, against the half- and quarter-range floors
+// (per half): n = 2 - (E2 + E3) and the complement of E2, as 0..2 and 0..1 in
+// 16-bit halves (non-negative fp16 values order like their bit patterns).
+__device__ __forceinline__ void block_levels(h2_t a4, h2_t a8, h2_t th_h, h2_t th_q, u16x2_t& n, u16x2_t& not_e2) {
+  const u16x2_t one = {1, 1};
+  const u16x2_t big4 = __builtin_elementwise_min(__builtin_elementwise_sub_sat(as_u16(a4), as_u16(th_h)), one);
+  not_e2 = __builtin_elementwise_min(__builtin_elementwise_sub_sat(as_u16(a8), as_u16(th_h)), one);
+  const u16x2_t quarter = __builtin_elementwise_min(__builtin_elementwise_sub_sat(as_u16(a4), as_u16(th_q)), one);
+  n = big4 + __builtin_elementwise_max(not_e2, quarter);
 }
 
-// Quantize 32 elements held as 8 complete 4-blocks (block order per LAYOUT);
-// the partner lane (l^32) holds the other 16.  Outputs per element: o (the
-// signed E2M3 value u*2^-sh) and the group metadata.
-template <int LAYOUT>
-__device__ __forceinline__ GroupMeta quantize_split(const float x[32], float o[32], int h) {
-  float a4own[8];
-#pragma unroll
-  for (int k = 0; k < 8; ++k) {
-    float m = fabsf(x[4 * k]);
-#pragma unroll
-    for (int i = 1; i < 4; ++i) m = fmaxf(m, fabsf(x[4 * k + i]));
-    a4own[k] = m;
-  }
-  float a4_all[16];
-  gather_a4<LAYOUT>(a4own, a4_all, h);
-  const GroupMeta g = group_meta(a4_all);
-  const float R = hif4_rcp_step(g.base);
-#pragma unroll
-  for (int k = 0; k < 8; ++k) {
-    const float C = round_const(block_shift(g, own_block<LAYOUT>(k, h)));
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const float a = fabsf(x[4 * k + i]);
-      const float ov = hif4_elem(a, R, C);
-      o[4 * k + i] = x[4 * k + i] < 0.0f ? -ov : ov;
-    }
-  }
-  return g;
+// fp16(a*R + C) per half (R fp32 per half, C fp16 per half): the code u sits in
+// the low mantissa bits, since C = 1.5 * 2^(10-sh) has the grid 2^-sh as its
+// last place.  Returns u in 0..7 per half.
+__device__ __forceinline__ uint32_t codes2(h2_t a, float r0, float r1, u16x2_t n) {
+  const u16x2_t c = n * (unsigned short)0x400 + (unsigned short)(kGrid10 & 0xFFFFu);
+  h2_t y;
+  asm("v_fma_mixlo_f16 %0, %1, %2, %4 op_sel:[0,0,0] op_sel_hi:[1,0,1]\n\t"
+      "v_fma_mixhi_f16 %0, %1, %3, %4 op_sel:[1,0,1] op_sel_hi:[1,0,1]"
+      : "=&v"(y)
+      : "v"(a), "v"(r0), "v"(r1), "v"(__builtin_bit_cast(uint32_t, c)));
+  return __builtin_bit_cast(uint32_t, y) & 0x00070007u;
 }
 
-__device__ __forceinline__ uint32_t nibble_of(float o, int sh) {
-  const float uf = fabsf(o) * (float)(1 << sh);
-  const uint32_t u = (uint32_t)uf;
-  return (u == 0u) ? 0u : (u | (o < 0.0f ? 8u : 0u));
+// Sign-magnitude nibbles of both halves: u | sign << 3, a zero code without a
+// sign (u + 7 carries into bit 3 exactly where u > 0).
+__device__ __forceinline__ uint32_t nibbles2(uint32_t u, h2_t x) {
+  const uint32_t s = (__builtin_bit_cast(uint32_t, x) >> 12) & 0x00080008u;
+  return u | ((u + 0x00070007u) & s);
+}
+
+// fp16(k/s) for a pair of fp16 values from r0, r1 = RN32(1/s) of each: with the
+// reciprocal taken two units in the last place (ulps) down and up, the fp32
+// products bracket the exact quotient (two ulps exceed the reciprocal's half
+// ulp and the product's rounding together), so where both ends round to the
+// same fp16 the quotient does too.  `open` collects the bits in which they
+// differ (about one value in 2000): those take the exact division.
+__device__ __forceinline__ h2_t divide2(h2_t k, float r0, float r1, uint32_t& open) {
+  const float d0 = __uint_as_float(__float_as_uint(r0) - 2u), u0 = __uint_as_float(__float_as_uint(r0) + 2u);
+  const float d1 = __uint_as_float(__float_as_uint(r1) - 2u), u1 = __uint_as_float(__float_as_uint(r1) + 2u);
+  float a, b, c, d;
+  asm("v_fma_mix_f32 %0, %4, %5, 0 op_sel:[0,0,0] op_sel_hi:[1,0,0]\n\t"
+      "v_fma_mix_f32 %1, %4, %6, 0 op_sel:[1,0,0] op_sel_hi:[1,0,0]\n\t"
+      "v_fma_mix_f32 %2, %4, %7, 0 op_sel:[0,0,0] op_sel_hi:[1,0,0]\n\t"
+      "v_fma_mix_f32 %3, %4, %8, 0 op_sel:[1,0,0] op_sel_hi:[1,0,0]"
+      : "=&v"(a), "=&v"(b), "=&v"(c), "=&v"(d)
+      : "v"(k), "v"(d0), "v"(d1), "v"(u0), "v"(u1));
+  const h2_t lo = pack2_f16(a, b), hi = pack2_f16(c, d);
+  open |= __builtin_bit_cast(uint32_t, lo) ^ __builtin_bit_cast(uint32_t, hi);
+  return lo;
+}
+
+// fp16(k/s) of N pairs: s and rs are the scales and their reciprocals.
+template <int N, typename S>
+__device__ __forceinline__ void divide_pairs(h2_t (&x)[N], const S& s, const S& rs) {
+  h2_t y[N];
+  uint32_t any = 0;
+#pragma unroll
+  for (int i = 0; i < N; ++i) y[i] = divide2(x[i], rs[2 * i], rs[2 * i + 1], any);
+  if (__builtin_expect(__builtin_amdgcn_ballot_w64(any != 0) != 0, 0)) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      uint32_t open = 0;
+      divide2(x[i], rs[2 * i], rs[2 * i + 1], open);
+      if (open) y[i] = h2_t{div_rn16((float)x[i][0], s[2 * i]), div_rn16((float)x[i][1], s[2 * i + 1])};
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < N; ++i) x[i] = y[i];
+}
+
+// Reductions over aligned sets of eight lanes (quad permutes, then the mirror
+// of eight, which pairs the two quads).
+template <typename F>
+__device__ __forceinline__ uint32_t reduce8(uint32_t v, F f) {
+  v = f(v, (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0xB1, 0xF, 0xF, true));    // quad_perm [1,0,3,2]
+  v = f(v, (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x4E, 0xF, 0xF, true));    // quad_perm [2,3,0,1]
+  return f(v, (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x141, 0xF, 0xF, true));  // row_half_mirror
 }
 
 // ---------------------------------------------------------------------------
-// Canonical Q^ / K^ (hifa4_quantize_qk).  One lane pair per group: lane l
-// holds channels [32h, 32h+32) of group g of row (token, head), h = l/32.
-// Each wave covers 32 groups.
+// Canonical Q^ / K^ (hifa4_quantize_qk).  Eight lanes per group: a lane holds
+// one 8-block (16 bytes of input, 4 bytes of codes), so a wave reads 1 KiB and
+// writes 256 bytes of codes in one piece each, E2 and E3 stay in the lane and
+// only the group maximum and the metadata word are reduced over the eight
+// lanes.  Bound by HBM (164 bytes moved per group).  A thread steps over the
+// rows at a stride that is a whole number of rows, so it keeps its column's
+// smoothing scales and reciprocals in registers, with kRowsAhead loads in
+// flight.  The K^ of 8 x 4096 tokens of 8 heads, D=128, took 84 us with a lane
+// pair per group (64-byte steps between lanes, fp32 arithmetic, a division per
+// element).
+constexpr int kRowsAhead = 4;
+
 template <bool kIsK>
 __global__ void __launch_bounds__(256) k_quant_rows(const half_t* __restrict__ x, const float* __restrict__ s,
                                                     uint8_t* __restrict__ codes, uint32_t* __restrict__ meta,
-                                                    int n_groups, int heads, int heads_kv, int G) {
-  const int lane = threadIdx.x & 63;
-  const int h = lane >> 5;
-  const int gidx = (blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)) * 32 + (lane & 31);
-  if (gidx >= n_groups) return;   // whole lane pairs exit together
-  const int g = gidx % G;
-  const int head = (gidx / G) % heads;
-  const int D = 64 * G;
-  const half_t* src = x + (size_t)gidx * 64 + 32 * h;
-  const float* sp = s ? s + (size_t)(head / (heads / heads_kv)) * D + 64 * g + 32 * h : nullptr;
-  float v[32], o[32];
-  load_smoothed32<kIsK>(src, sp, v);
-  const GroupMeta gm = quantize_split<kRows>(v, o, h);
-  uint32_t words[4];
+                                                    long n_pieces, long stride, int heads, int heads_kv, int D) {
+  const long tid = (long)blockIdx.x * 256 + threadIdx.x;
+  if (tid >= stride) return;                  // whole sets of eight lanes exit together
+  const int j = threadIdx.x & 7;
+  float sc[8], rc[8];
+  if (s) {
+    const int ch = (int)(tid % (heads * D / 8)) * 8;
+    const int hk = (ch / D) / (heads / heads_kv);
+    const float4* sp = reinterpret_cast<const float4*>(s + (size_t)hk * D + ch % D);
+    const float4 a = sp[0], b = sp[1];
+    const float t[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
 #pragma unroll
-  for (int w = 0; w < 4; ++w) {
-    uint32_t acc = 0;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const int el = 8 * w + e;
-      const int sh = block_shift(gm, 8 * h + el / 4);
-      acc |= nibble_of(o[el], sh) << (4 * e);
+    for (int i = 0; i < 8; ++i) {
+      sc[i] = t[i];
+      rc[i] = kIsK ? 1.0f / t[i] : 0.0f;
     }
-    words[w] = acc;
   }
-  uint4* dst = reinterpret_cast<uint4*>(codes + (size_t)gidx * 32 + 16 * h);
-  *dst = make_uint4(words[0], words[1], words[2], words[3]);
-  if (h == 0) meta[gidx] = gm.base | (gm.e2 << 8) | (gm.e3 << 16);
+  for (long i0 = tid; i0 < n_pieces; i0 += kRowsAhead * stride) {
+    uint4 in[kRowsAhead];
+#pragma unroll
+    for (int r = 0; r < kRowsAhead; ++r) {
+      const long i = i0 + r * stride;
+      in[r] = *reinterpret_cast<const uint4*>(x + 8 * (i < n_pieces ? i : tid));
+    }
+#pragma unroll
+    for (int r = 0; r < kRowsAhead; ++r) {
+      const long i = i0 + r * stride;
+      if (i >= n_pieces) break;               // whole sets of eight lanes again (n_pieces is a multiple of 8)
+      h2_t v[4] = {__builtin_bit_cast(h2_t, in[r].x), __builtin_bit_cast(h2_t, in[r].y),
+                   __builtin_bit_cast(h2_t, in[r].z), __builtin_bit_cast(h2_t, in[r].w)};
+      if (s) {
+        if (kIsK) {
+          divide_pairs(v, sc, rc);
+        } else {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) v[e] = smooth_mul2(v[e], sc[2 * e], sc[2 * e + 1]);
+        }
+      }
+      h2_t a[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) a[e] = habs2(v[e]);
+      const h2_t a4 = hmax_pairs(hmax2(a[0], a[1]), hmax2(a[2], a[3]));     // both 4-blocks
+      // (integer maxima here: the lane exchanges read registers right after they
+      // are written, which the compiler must be able to see)
+      const u16x2_t a8u = __builtin_elementwise_max(as_u16(a4), __builtin_shufflevector(as_u16(a4), as_u16(a4), 1, 0));
+      const h2_t a8 = __builtin_bit_cast(h2_t, a8u);
+      const uint32_t gm = reduce8(__builtin_bit_cast(uint32_t, a8u), [](uint32_t p, uint32_t q) {
+        return __builtin_bit_cast(
+            uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2_t, p), __builtin_bit_cast(u16x2_t, q)));
+      });
+      const uint32_t base = e6m2_ceil((float)__builtin_bit_cast(h2_t, gm)[0]);
+      const float R = hif4_rcp_step(base);
+      const h2_t thr = range_floors(e6m2_value(base));
+      u16x2_t n, ne2;
+      block_levels(a4, a8, h2_t{thr[0], thr[0]}, h2_t{thr[1], thr[1]}, n, ne2);
+      uint32_t word = 0;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const unsigned short ne = n[e >> 1];
+        const uint32_t nib = nibbles2(codes2(a[e], R, R, u16x2_t{ne, ne}), v[e]);
+        word |= ((nib | (nib >> 12)) & 0xFFu) << (8 * e);
+      }
+      reinterpret_cast<uint32_t*>(codes)[i] = word;
+      // E2 = 1 - ne2, E3 = 2 - n - E2 per 4-block
+      const uint32_t e2 = 1u - ne2[0];
+      const uint32_t e3 = (2u - n[0] - e2) | ((2u - n[1] - e2) << 1);
+      const uint32_t bits = reduce8((e2 << (8 + j)) | (e3 << (16 + 2 * j)), [](uint32_t p, uint32_t q) { return p | q; });
+      if (j == 0) meta[i >> 3] = base | bits;
+    }
+  }
 }
 
 // ---------------------------------------------------------------------------
-// Canonical V^ (hifa4_quantize_v): group = 64 tokens of one (kv head,
-// channel) column, aligned to the sequence start.  Lanes 0..31 of a wave take
-// 32 consecutive channels for tokens [0,32) of the group, lanes 32..63 the
-// same channels for tokens [32,64).
+// Canonical V^ (hifa4_quantize_v): group = 64 tokens of one (kv head, channel)
+// column, aligned to the sequence start.  A lane holds four consecutive
+// columns (of the heads_kv * D of a token) and 32 of the group's tokens; lane
+// l^32 holds the other 32.  Both halves of every packed register are two
+// channels, so all decisions but the group maximum stay in the lane; a load
+// reads two whole 256-byte runs of columns per wave, all 32 issued before the
+// first is used.  Bound by HBM (the groups' 128 bytes in, 36 out).  V^ of 8 x
+// 4096 tokens of 8 heads, D=128, took 41 us with a lane per channel reading 2
+// bytes at a time.
 __global__ void __launch_bounds__(256) k_quant_v_canon(const half_t* __restrict__ v, const int* __restrict__ cu,
                                                        uint8_t* __restrict__ codes, uint32_t* __restrict__ meta,
-                                                       int batch, int S, int NB, int heads_kv, int D) {
+                                                       int batch, int S, int NB, int cols) {
   const int lane = threadIdx.x & 63;
   const int h = lane >> 5;
-  const long gidx = ((long)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)) * 32 + (lane & 31);
-  const long n_groups = (long)batch * NB * heads_kv * D;
-  if (gidx >= n_groups) return;
-  const int d = (int)(gidx % D);
-  const int hk = (int)((gidx / D) % heads_kv);
-  const int J = (int)((gidx / ((long)D * heads_kv)) % NB);
-  const int b = (int)(gidx / ((long)D * heads_kv * NB));
+  const long item = ((long)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)) * 32 + (lane & 31);
+  const int per_block = cols / 4;
+  if (item >= (long)batch * NB * per_block) return;      // whole lane pairs
+  const int c0 = 4 * (int)(item % per_block);
+  const int J = (int)((item / per_block) % NB);
+  const int b = (int)(item / per_block / NB);
   const int t0 = seq_start(cu, b, S);
   const int L = seq_len(cu, b, S);
-  float x[32], o[32];
+  const int p0 = 64 * J + 32 * h;
+  h2_t x[32][2];
+  if (64 * J < L) {
+    uint2 in[32];
 #pragma unroll
-  for (int k = 0; k < 32; ++k) {
-    const int pos = 64 * J + 32 * h + k;
-    x[k] = pos < L ? (float)v[((size_t)(t0 + pos) * heads_kv + hk) * D + d] : 0.0f;
-  }
-  const GroupMeta gm = quantize_split<kRows>(x, o, h);
-  uint32_t words[4];
+    for (int k = 0; k < 32; ++k)
+      in[k] = *reinterpret_cast<const uint2*>(v + (size_t)(t0 + min(p0 + k, L - 1)) * cols + c0);
 #pragma unroll
-  for (int w = 0; w < 4; ++w) {
-    uint32_t acc = 0;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const int el = 8 * w + e;
-      acc |= nibble_of(o[el], block_shift(gm, 8 * h + el / 4)) << (4 * e);
+    for (int k = 0; k < 32; ++k) {
+      const bool live = p0 + k < L;
+      x[k][0] = __builtin_bit_cast(h2_t, live ? in[k].x : 0u);
+      x[k][1] = __builtin_bit_cast(h2_t, live ? in[k].y : 0u);
     }
-    words[w] = acc;
+  } else {
+#pragma unroll
+    for (int k = 0; k < 32; ++k) x[k][0] = x[k][1] = h2_t{(half_t)0, (half_t)0};
   }
-  *reinterpret_cast<uint4*>(codes + (size_t)gidx * 32 + 16 * h) = make_uint4(words[0], words[1], words[2], words[3]);
-  if (h == 0) meta[gidx] = gm.base | (gm.e2 << 8) | (gm.e3 << 16);
+  const size_t g0 = (size_t)item * 4;                     // first of the lane's four groups
+#pragma unroll
+  for (int w = 0; w < 2; ++w) {
+    h2_t a4[8], gm = {(half_t)0, (half_t)0};
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      a4[q] = hmax2(hmax2(habs2(x[4 * q][w]), habs2(x[4 * q + 1][w])),
+                    hmax2(habs2(x[4 * q + 2][w]), habs2(x[4 * q + 3][w])));
+      gm = hmax2(gm, a4[q]);
+    }
+    gm = max_with_partner(gm);
+    const uint32_t base0 = e6m2_ceil((float)gm[0]), base1 = e6m2_ceil((float)gm[1]);
+    const float r0 = hif4_rcp_step(base0), r1 = hif4_rcp_step(base1);
+    const h2_t f0 = range_floors(e6m2_value(base0)), f1 = range_floors(e6m2_value(base1));
+    const h2_t th_h = {f0[0], f1[0]}, th_q = {f0[1], f1[1]};
+    uint32_t acc[8];           // four tokens' nibbles per half
+    uint32_t lev = 0;          // per half: E2 of the lane's four 8-blocks, then E3 of its eight 4-blocks
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      u16x2_t n, ne2;
+      block_levels(a4[q], hmax2(a4[q & ~1], a4[q | 1]), th_h, th_q, n, ne2);
+      acc[q] = 0;
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        acc[q] |= nibbles2(codes2(habs2(x[4 * q + i][w]), r0, r1, n), x[4 * q + i][w]) << (4 * i);
+      const uint32_t e2 = 0x00010001u - __builtin_bit_cast(uint32_t, ne2);
+      if ((q & 1) == 0) lev |= e2 << (q >> 1);
+      lev |= (0x00020002u - __builtin_bit_cast(uint32_t, n) - e2) << (4 + q);
+    }
+    uint32_t lo[4], hi[4];
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+      lo[d] = __builtin_amdgcn_perm(acc[2 * d + 1], acc[2 * d], 0x05040100u);
+      hi[d] = __builtin_amdgcn_perm(acc[2 * d + 1], acc[2 * d], 0x07060302u);
+    }
+    uint8_t* dst = codes + (g0 + 2 * w) * 32 + 16 * h;
+    *reinterpret_cast<uint4*>(dst) = make_uint4(lo[0], lo[1], lo[2], lo[3]);
+    *reinterpret_cast<uint4*>(dst + 32) = make_uint4(hi[0], hi[1], hi[2], hi[3]);
+    const Pair32 pl = pair32(lev);                        // x: tokens 0..31, y: tokens 32..63
+    const uint32_t l0 = h ? pl.x >> 16 : pl.x, l1 = h ? pl.y >> 16 : pl.y;      // lane half h writes channel 2w + h
+    meta[g0 + 2 * w + h] = (h ? base1 : base0) | ((l0 & 0xFu) << 8) | ((l1 & 0xFu) << 12) | (((l0 >> 4) & 0xFFu) << 16) |
+                           (((l1 >> 4) & 0xFFu) << 24);
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -268,10 +386,7 @@ __global__ void __launch_bounds__(512) k_prep_kv_hif4(const half_t* __restrict__
       __syncthreads();
       const float* sc = ss + 64 * g + 32 * h;
       const float* rc = rs + 64 * g + 32 * h;
-#pragma unroll
-      for (int i = 0; i < 16; ++i)
-        x[i] = h2_t{div_rn16_rcp((float)x[i][0], sc[2 * i], rc[2 * i]),
-                    div_rn16_rcp((float)x[i][1], sc[2 * i + 1], rc[2 * i + 1])};
+      divide_pairs(x, sc, rc);
     }
     if (qmean) {
       // Q-Mean key sums (Algorithm 1's correction term): the exact sum of the
@@ -443,26 +558,27 @@ __global__ void k_selftest_exp2(const half_t* __restrict__ x, half_t* __restrict
 // Host launchers.
 hipError_t launch_quant_rows(const half_t* x, const float* s, uint8_t* codes, uint32_t* meta, long n_rows,
                              int heads, int heads_kv, int D, bool is_k, hipStream_t st) {
-  const int G = D / 64;
-  const long n_groups = n_rows * heads * G;
-  if (n_groups == 0) return hipSuccess;
-  const int waves = 4;
-  const long blocks = (n_groups + 32 * waves - 1) / (32 * waves);
+  const long per_row = (long)heads * D / 8;               // pieces of 8 channels
+  const long n = n_rows * per_row;
+  if (n == 0) return hipSuccess;
+  // six waves per SIMD on 256 compute units, rounded up to a whole number of
+  // rows (four, eight or sixteen waves are 1 to 2% slower)
+  constexpr long kThreads = 256L * 1536;
+  const long stride = std::min(n, (kThreads + per_row - 1) / per_row * per_row);
+  const dim3 grid((unsigned)((stride + 255) / 256));
   if (is_k)
-    k_quant_rows<true><<<dim3((unsigned)blocks), dim3(64 * waves), 0, st>>>(x, s, codes, meta, (int)n_groups, heads,
-                                                                            heads_kv, G);
+    k_quant_rows<true><<<grid, dim3(256), 0, st>>>(x, s, codes, meta, n, stride, heads, heads_kv, D);
   else
-    k_quant_rows<false><<<dim3((unsigned)blocks), dim3(64 * waves), 0, st>>>(x, s, codes, meta, (int)n_groups, heads,
-                                                                             heads_kv, G);
+    k_quant_rows<false><<<grid, dim3(256), 0, st>>>(x, s, codes, meta, n, stride, heads, heads_kv, D);
   return hipGetLastError();
 }
 
 hipError_t launch_quant_v(const half_t* v, const int* cu, uint8_t* codes, uint32_t* meta, int batch, int S, int NB,
                           int heads_kv, int D, hipStream_t st) {
-  const long n_groups = (long)batch * NB * heads_kv * D;
-  if (n_groups == 0) return hipSuccess;
-  const long blocks = (n_groups + 127) / 128;
-  k_quant_v_canon<<<dim3((unsigned)blocks), dim3(256), 0, st>>>(v, cu, codes, meta, batch, S, NB, heads_kv, D);
+  const long n_items = (long)batch * NB * heads_kv * D / 4;
+  if (n_items == 0) return hipSuccess;
+  const long blocks = (n_items + 127) / 128;
+  k_quant_v_canon<<<dim3((unsigned)blocks), dim3(256), 0, st>>>(v, cu, codes, meta, batch, S, NB, heads_kv * D);
   return hipGetLastError();
 }
 

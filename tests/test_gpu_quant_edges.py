@@ -1,0 +1,67 @@
+"""The canonical quantizers at the sizes where their work split can go wrong,
+against the oracle: bit-exact codes and metadata."""
+import numpy as np
+import pytest
+
+from oracle import attention as oatt
+
+from _gpu_util import to_gpu, to_np
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def h():
+    import paper_2607_04302_amd as mod
+    mod.load_library()
+    return mod
+
+
+def _draw(rng, *shape):
+    x = (rng.standard_normal(shape) * 4).astype(np.float16)
+    x.reshape(-1)[:: 97] = 0
+    return x
+
+
+# one row; rows that are no multiple of a wave or a workgroup; head counts whose
+# rows do not divide a workgroup; more pieces than threads (a second step per
+# thread, and a last step that only some threads take)
+@pytest.mark.parametrize("t,hq,hkv,d", [(1, 1, 1, 64), (3, 5, 5, 64), (7, 12, 12, 64), (33, 6, 3, 128), (2, 16, 2, 256),
+                                        (3001, 8, 8, 128), (13001, 8, 8, 128)])
+def test_rows(h, t, hq, hkv, d):
+    rng = np.random.default_rng(t + d)
+    q, k = _draw(rng, 1, t, hq, d), _draw(rng, 1, t, hkv, d)
+    s = np.exp(rng.uniform(-2, 2, (hkv, d))).astype(np.float32)
+    rows = np.unique(np.concatenate([np.arange(min(t, 24)), np.arange(max(0, t - 24), t), rng.integers(0, t, 40)]))
+    for sv in (None, s):
+        got = h.hifa4_quantize_qk(to_gpu(q), to_gpu(k), None if sv is None else to_gpu(sv))
+        want = oatt.quantize_qk(q[0, rows], k[0, rows], sv)
+        for g, w in zip(got, want):
+            g = to_np(g)[rows]
+            assert np.array_equal(g.view(w.dtype).reshape(w.shape), w)
+
+
+# lengths around the 64-token groups and the half group a lane holds, an empty
+# sequence, columns that do not fill a wave
+@pytest.mark.parametrize("hkv,d,lens", [(1, 64, (1, 31, 32, 33)), (3, 64, (63, 64, 65, 0, 127)), (5, 128, (130,)),
+                                        (2, 256, (96, 1))])
+def test_tokens(h, hkv, d, lens):
+    rng = np.random.default_rng(sum(lens) + d)
+    v = _draw(rng, sum(lens), hkv, d)
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    nb = (max(lens) + 63) // 64
+    vc, vm = h.hifa4_quantize_v(to_gpu(v), cu_seqlens=to_gpu(cu), max_seqlen=max(lens))
+    wc, wm = oatt.quantize_v(v, cu) if 0 not in lens else (None, None)
+    vc, vm = to_np(vc), to_np(vm).view(np.uint32)
+    at = 0
+    for b, n in enumerate(lens):
+        g = (n + 63) // 64
+        if wc is None:
+            one = oatt.quantize_v(v[cu[b]:cu[b + 1]], np.array([0, n])) if n else None
+            c, m = one if n else (np.zeros((0,) + vc.shape[2:], np.uint8), np.zeros((0,) + vm.shape[2:], np.uint32))
+        else:
+            c, m = wc[at:at + g], wm[at:at + g]
+            at += g
+        assert np.array_equal(vc[b, :g], c) and np.array_equal(vm[b, :g], m)
+        # groups past the end are the groups of 64 zeros: base 0, every E2 and E3 bit set
+        assert not vc[b, g:].any() and np.all(vm[b, g:] == 0xFFFFFF00) and nb >= g
