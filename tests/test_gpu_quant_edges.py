@@ -1,9 +1,11 @@
-"""The canonical quantizers at the sizes where their work split can go wrong,
-against the oracle: bit-exact codes and metadata."""
+"""The canonical quantizers and the calibration pass at the sizes where their
+work split can go wrong, against the oracle: bit-exact codes, metadata and gate
+statistics, scales within one fp32 ulp."""
 import numpy as np
 import pytest
 
 from oracle import attention as oatt
+from oracle import smooth as osmooth
 
 from _gpu_util import to_gpu, to_np
 
@@ -65,3 +67,21 @@ def test_tokens(h, hkv, d, lens):
         assert np.array_equal(vc[b, :g], c) and np.array_equal(vm[b, :g], m)
         # groups past the end are the groups of 64 zeros: base 0, every E2 and E3 bit set
         assert not vc[b, g:].any() and np.all(vm[b, g:] == 0xFFFFFF00) and nb >= g
+
+
+# fewer tokens than workgroups; runs that cross sequences; pieces that do not
+# divide a workgroup; more pieces than threads
+@pytest.mark.parametrize("n,s,hq,hkv,d", [(1, 1, 1, 1, 64), (3, 37, 10, 5, 64), (2, 700, 12, 12, 128), (5, 211, 8, 2, 256),
+                                          (1, 9, 40, 40, 256)])
+def test_calibration(h, n, s, hq, hkv, d):
+    rng = np.random.default_rng(n * s + d)
+    q, k = _draw(rng, n, s, hq, d), _draw(rng, n, s, hkv, d)
+    k[..., 3] *= np.float16(9)
+    for alpha in (-1.0, 0.5):
+        sg, rep = h.hifa4_calibrate_smooth_qk(to_gpu(q), to_gpu(k), alpha)
+        sw, want = osmooth.calibrate(q, k, hkv, alpha)
+        assert rep["branch"] == want["branch"]
+        assert abs(rep["rho_k"] - want["rho_k"]) <= 1e-9 * want["rho_k"]
+        assert abs(rep["t_kq"] - want["t_kq"]) <= 1e-9 * want["t_kq"]
+        ulps = np.abs(to_np(sg).view(np.int32).astype(np.int64) - sw.view(np.int32).astype(np.int64))
+        assert ulps.max() <= 1
