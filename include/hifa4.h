@@ -310,9 +310,9 @@ size_t hifa4_decode_workspace_bytes(const hifa4_problem* p);
  *    HIFA4_ERR_UNSUPPORTED; num_heads_q / num_heads_kv must be <= 8 (else
  *    HIFA4_ERR_UNSUPPORTED).
  * workspace: DEVICE, >= hifa4_decode_workspace_bytes(p).  Asynchronous.
- * Where the splits of the key range fill the GPU (at least 256 workgroups),
- * scores and splits run in one kernel in which each split waits, with a
- * bounded spin, for the run maxima that the splits before it in the same row
+ * The blocks of a sequence are cut into runs (splits), one kernel takes their
+ * scores and their partial outputs, and each run waits, with a bounded spin,
+ * for the run maxima that the runs before it in the same row
  * publish (tagged with a per-call value; the last kernel of the call clears
  * them, so no word of an earlier call, eager or replayed from a graph,
  * satisfies a wait).  The waits end because every GPU engine dispatches the

@@ -1,0 +1,49 @@
+"""Decode step: every way a call's blocks become runs.  Run lengths of 1 to 8
+blocks, odd and even, runs numbered over the sequences' own lengths (up to 256
+sequences, the prefix sum over the batch in one to four steps) or over the
+longest one (more sequences, or no cu_seqlens), last blocks of 1 to 64 keys,
+empty sequences, four and eight waves per workgroup.  Every P^ code of the
+sampled rows bit-exact against the oracle, O and LSE within the parity bar."""
+import numpy as np
+import pytest
+
+from paper_2607_04302_amd.workloads import small_case
+
+from test_gpu_decode import _decode_and_compare, _say, h  # noqa: F401  (h: the library fixture)
+
+pytestmark = pytest.mark.gpu
+
+
+def _lens(n, lo, hi, seed, empty=()):
+    x = np.random.default_rng(seed).integers(lo, hi + 1, n)
+    x[list(empty)] = 0
+    return tuple(int(v) for v in x)
+
+
+@pytest.mark.parametrize("lens,d,hq,hkv,seqs,kv_heads", [
+    ((64, 65, 127, 128, 1, 63), 128, 8, 2, None, None),                  # runs of 1, every kind of last block
+    (_lens(70, 1, 200, 1, empty=(0, 63, 64)), 64, 2, 1, [1, 62, 65, 69], None),     # two steps of the prefix sum
+    (_lens(200, 1, 90, 2, empty=(199,)), 128, 4, 1, [0, 127, 128, 198], None),       # four steps
+    (_lens(300, 1, 150, 3, empty=(5, 299)), 64, 1, 1, [0, 4, 256, 298], None),       # above 256 sequences
+    ((2999, 3300, 70, 3265), 64, 64, 64, [0, 2, 3], [0, 63]),            # runs of 3
+    ((4001, 4100, 3900, 4096, 64), 64, 64, 64, [1, 4], [5]),             # runs of 5
+    ((5000, 4097, 63), 256, 16, 16, [0, 1, 2], [0, 15]),                 # D = 256: four waves, runs of 2
+    ((3000, 2047), 256, 40, 8, [0, 1], [7]),                             # two rows per lane, GQA x5
+])
+def test_decode_run_shapes(h, lens, d, hq, hkv, seqs, kv_heads):  # noqa: F811
+    _, k, v, cu = small_case(heads_q=hkv, heads_kv=hkv, head_dim=d, seqlens=lens, seed=41)
+    qd = np.random.default_rng(42).standard_normal((len(lens), hq, d)).astype(np.float16)
+    s = np.exp(np.random.default_rng(43).uniform(-1, 1, (hkv, d))).astype(np.float32)
+    _say("decode runs", len(lens), max(lens), d, hq, hkv)
+    _decode_and_compare(h, qd, k, v, cu, s, max(lens), seqs=seqs, kv_heads=kv_heads)
+
+
+@pytest.mark.parametrize("norm", ["preorder", "inconsistent"])
+def test_decode_max_seqlen_above_every_length(h, norm):  # noqa: F811
+    """max_seqlen as an upper bound (a preallocated cache): the grid follows
+    the cached tokens, the V^ cache and the P^ dump the bound."""
+    lens = (700, 0, 65, 1)
+    _, k, v, cu = small_case(heads_q=2, heads_kv=2, head_dim=128, seqlens=lens, seed=44)
+    qd = np.random.default_rng(45).standard_normal((len(lens), 8, 128)).astype(np.float16)
+    _say("decode bound above lengths", norm)
+    _decode_and_compare(h, qd, k, v, cu, None, 5000, norm=norm)
