@@ -179,8 +179,8 @@ size_t hifa4_calibrate_workspace_bytes(const hifa4_problem* p, int32_t n_calib);
  * (n_calib fixed-length sequences stacked on the leading axis; p->batch and
  * p->cu_seqlens are ignored).  Per sequence, the GPU reduces max|K| over
  * tokens and max|Q| over tokens and the query heads of each group, per (kv
- * head, channel), and a 32768-bin histogram of |K| (exact for fp16).  On the
- * host, in float64: the RMS over sequences, s = Kbar^alpha / Qbar^(1-alpha)
+ * head, channel), and a 32768-bin histogram of |K| (exact for fp16).  Then, in
+ * float64 on the GPU: the RMS over sequences, s = Kbar^alpha / Qbar^(1-alpha)
  * rounded once to fp32 (s = 1 where a statistic is 0 or s is not finite),
  * and the gate statistics rho_K = max|K| / P99|K| (linear interpolation
  * between order statistics) and T = max|K| / max|Q|.

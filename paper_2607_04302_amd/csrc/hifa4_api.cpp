@@ -1,5 +1,5 @@
 // C ABI of libhifa4 (declared in include/hifa4.h): argument validation,
-// workspace carving, kernel launches and the host side of calibration.
+// workspace carving and kernel launches.
 #include "../../include/hifa4.h"
 
 #include <hip/hip_runtime.h>
@@ -12,7 +12,6 @@
 #include <initializer_list>
 #include <mutex>
 #include <string>
-#include <vector>
 
 #include "hifa4_decode.h"
 #include "hifa4_internal.h"
@@ -302,88 +301,17 @@ hifa4_status hifa4_calibrate_smooth_qk(const hifa4_problem* p, int32_t n_calib, 
   unsigned long long* hist = (unsigned long long*)((uint8_t*)workspace + hifa4::round_up256(n_stats * 4));
   hipStream_t hs = (hipStream_t)stream;
   hipError_t e = hifa4::launch_calib((const hifa4::half_t*)q_calib, (const hifa4::half_t*)k_calib, n_calib, S,
-                                     p->num_heads_q, hkv, D, stats, hist, hs);
+                                     p->num_heads_q, hkv, D, alpha, stats, hist, s_out, hs);
   if (e != hipSuccess) return hip_fail(e, "calibration kernels");
-  std::vector<uint32_t> hs_stats(n_stats);
-  std::vector<unsigned long long> hh(32768);
-  e = hipMemcpyAsync(hs_stats.data(), stats, n_stats * 4, hipMemcpyDeviceToHost, hs);
-  if (e == hipSuccess) e = hipMemcpyAsync(hh.data(), hist, 32768 * 8, hipMemcpyDeviceToHost, hs);
+  hifa4::CalibGate gate;
+  e = hipMemcpyAsync(&gate, hist, sizeof gate, hipMemcpyDeviceToHost, hs);
   if (e == hipSuccess) e = hipStreamSynchronize(hs);
   if (e != hipSuccess) return hip_fail(e, "calibration copy-back");
-
-  auto f32 = [](uint32_t u) { float f; std::memcpy(&f, &u, 4); return (double)f; };
-  // RMS over calibration sequences of the per-sequence maxima (float64).
-  std::vector<double> kbar((size_t)hkv * D), qbar((size_t)hkv * D);
-  double kmax_all = 0.0, qmax_all = 0.0;
-  for (size_t i = 0; i < (size_t)hkv * D; ++i) {
-    double sk = 0.0, sq = 0.0;
-    for (int n = 0; n < n_calib; ++n) {
-      const double kv = f32(hs_stats[((size_t)n * 2 + 0) * hkv * D + i]);
-      const double qv = f32(hs_stats[((size_t)n * 2 + 1) * hkv * D + i]);
-      sk += kv * kv;
-      sq += qv * qv;
-      kmax_all = std::max(kmax_all, kv);
-      qmax_all = std::max(qmax_all, qv);
-    }
-    kbar[i] = std::sqrt(sk / n_calib);
-    qbar[i] = std::sqrt(sq / n_calib);
-  }
-  // P99 of |K| with linear interpolation between order statistics.
-  unsigned long long total = 0;
-  for (int i = 0; i < 32768; ++i) total += hh[i];
-  auto order_stat = [&](unsigned long long k) {
-    unsigned long long c = 0;
-    for (int i = 0; i < 32768; ++i) {
-      c += hh[i];
-      if (c > k) {
-        const uint16_t bits = (uint16_t)i;
-        const _Float16 hv = __builtin_bit_cast(_Float16, bits);
-        return (double)(float)hv;
-      }
-    }
-    return 0.0;
-  };
-  double p99 = 0.0;
-  if (total > 0) {
-    const double pos = 0.99 * (double)(total - 1);
-    const unsigned long long lo = (unsigned long long)std::floor(pos);
-    const double t = pos - (double)lo;
-    const double a = order_stat(lo), b = order_stat(std::min(lo + 1, total - 1));
-    const double diff = b - a;
-    p99 = t >= 0.5 ? b - diff * (1.0 - t) : a + diff * t;
-  }
-  const double rho = p99 > 0 ? kmax_all / p99 : INFINITY;
-  const double tkq = qmax_all > 0 ? kmax_all / qmax_all : INFINITY;
-  int branch;
-  double a_used;
-  if (alpha < 0) {
-    if (rho >= 6.0 && tkq > 3.0) branch = 2;
-    else if (rho >= 6.0 && tkq >= 2.0 && tkq <= 3.0) branch = 1;
-    else branch = 0;
-    a_used = branch == 2 ? 0.5 : (branch == 1 ? 0.25 : 0.0);
-  } else if (alpha == 0) {
-    branch = 0;
-    a_used = 0.0;
-  } else {
-    branch = alpha >= 0.5f ? 2 : 1;
-    a_used = alpha;
-  }
-  std::vector<float> sv((size_t)hkv * D, 1.0f);
-  if (a_used != 0.0) {
-    for (size_t i = 0; i < sv.size(); ++i) {
-      const double s = std::pow(kbar[i], a_used) / std::pow(qbar[i], 1.0 - a_used);
-      const bool bad = kbar[i] == 0 || qbar[i] == 0 || !std::isfinite(s) || s == 0;
-      sv[i] = bad ? 1.0f : (float)s;
-    }
-  }
-  e = hipMemcpyAsync(s_out, sv.data(), sv.size() * 4, hipMemcpyHostToDevice, hs);
-  if (e == hipSuccess) e = hipStreamSynchronize(hs);
-  if (e != hipSuccess) return hip_fail(e, "calibration scale upload");
   if (report) {
-    report->rho_k = rho;
-    report->t_kq = tkq;
-    report->branch = branch;
-    report->alpha_used = (float)a_used;
+    report->rho_k = gate.rho;
+    report->t_kq = gate.t_kq;
+    report->branch = gate.branch;
+    report->alpha_used = (float)gate.alpha;
   }
   return HIFA4_OK;
 }

@@ -83,8 +83,13 @@ hipError_t launch_quant_v(const half_t* v, const int* cu, uint8_t* codes, uint32
                           int heads_kv, int D, hipStream_t st);
 hipError_t launch_prep_kv(const half_t* k, const half_t* v, const float* s, const int* cu, uint8_t* ws, int batch,
                           int S, int NB, int heads_kv, int D, bool fp16, bool qmean, hipStream_t st);
-hipError_t launch_calib(const half_t* q, const half_t* k, int n, int S, int hq, int hkv, int D, uint32_t* stats,
-                        unsigned long long* hist, hipStream_t st);
+// What calibration leaves at the start of `hist`: the report and the alpha used.
+struct CalibGate {
+  double rho, t_kq, alpha;
+  int branch;
+};
+hipError_t launch_calib(const half_t* q, const half_t* k, int n, int S, int hq, int hkv, int D, float alpha,
+                        uint32_t* stats, unsigned long long* hist, float* s_out, hipStream_t st);
 hipError_t launch_selftest_exp2(const half_t* x, half_t* y, long n, hipStream_t st);
 // operands: 0 HIF4, 1 FP16 reference, 2 P-only (fp16 Q, K, V; HIF4 P)
 hipError_t launch_attention(const AttnArgs& a, int norm, int operands, bool qmean, hipStream_t st);

@@ -610,6 +610,132 @@ __global__ void __launch_bounds__(kCalibThreads) k_calib(CalibArgs a) {
 }
 
 // ---------------------------------------------------------------------------
+// The gate of one layer, in float64: one workgroup reads the histogram (each
+// thread a run of bins) and the channel maxima, and leaves rho, T, the branch
+// and alpha in place of the first bins.  The formulas are evaluated step by
+// step (no contraction into fused multiply-adds).
+//
+// Both kernels replace a copy of the statistics to the host and the same sums
+// there: 390 KB through pageable memory, three passes over the bins and two
+// pow() per channel: 273 us a call before, 198 us with it (16 x 4096 tokens, 32 + 8
+// heads, D = 128), of which the pass over Q and K takes 145 us.
+constexpr int kGateThreads = 1024;
+
+__global__ void __launch_bounds__(kGateThreads) k_calib_gate(const uint32_t* __restrict__ stats,
+                                                             unsigned long long* hist, int n, int hd, float alpha) {
+#pragma clang fp contract(off)
+  constexpr int kPer = kCalibBins / kGateThreads, kWaves = kGateThreads / 64;
+  __shared__ unsigned long long wave_sum[kWaves];
+  __shared__ float wave_max[2][kWaves];
+  __shared__ double stat_at[2];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  unsigned long long c[kPer], own = 0;
+#pragma unroll
+  for (int i = 0; i < kPer; ++i) c[i] = hist[kPer * tid + i];
+  // largest statistic of K and of Q (a NaN never replaces a maximum)
+  float mk = 0.0f, mq = 0.0f;
+  for (int r = 0; r < n; ++r)
+    for (int i = tid; i < hd; i += kGateThreads) {
+      const float k = __uint_as_float(stats[(size_t)(2 * r) * hd + i]);
+      const float q = __uint_as_float(stats[(size_t)(2 * r + 1) * hd + i]);
+      mk = mk < k ? k : mk;
+      mq = mq < q ? q : mq;
+    }
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const float k = __shfl_xor(mk, o), q = __shfl_xor(mq, o);
+    mk = mk < k ? k : mk;
+    mq = mq < q ? q : mq;
+  }
+#pragma unroll
+  for (int i = 0; i < kPer; ++i) own += c[i];
+  unsigned long long incl = own;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const unsigned long long t = __shfl_up(incl, o);
+    if (lane >= o) incl += t;
+  }
+  if (lane == 63) wave_sum[wave] = incl;
+  if (lane == 0) {
+    wave_max[0][wave] = mk;
+    wave_max[1][wave] = mq;
+  }
+  if (tid < 2) stat_at[tid] = 0.0;
+  __syncthreads();
+  unsigned long long before = incl - own, total = 0;
+  for (int w = 0; w < kWaves; ++w) {
+    if (w < wave) before += wave_sum[w];
+    total += wave_sum[w];
+    mk = mk < wave_max[0][w] ? wave_max[0][w] : mk;
+    mq = mq < wave_max[1][w] ? wave_max[1][w] : mq;
+  }
+  // P99 of |K|: linear interpolation between two order statistics
+  const double pos = total > 0 ? 0.99 * (double)(total - 1) : 0.0;
+  const unsigned long long lo = (unsigned long long)floor(pos);
+  const unsigned long long hi = total > 0 && lo + 1 > total - 1 ? total - 1 : lo + 1;
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    const unsigned long long k = j == 0 ? lo : hi;
+    if (k < before || k >= before + own) continue;        // the bin that holds it is another thread's
+    unsigned long long at = before;
+    bool found = false;
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+      at += c[i];
+      if (!found && at > k) {
+        stat_at[j] = (double)(float)__builtin_bit_cast(half_t, (uint16_t)(kPer * tid + i));
+        found = true;
+      }
+    }
+  }
+  __syncthreads();
+  if (tid != 0) return;
+  double p99 = 0.0;
+  if (total > 0) {
+    const double t = pos - (double)lo, a = stat_at[0], b = stat_at[1], diff = b - a;
+    p99 = t >= 0.5 ? b - diff * (1.0 - t) : a + diff * t;
+  }
+  CalibGate g;
+  g.rho = p99 > 0 ? (double)mk / p99 : __builtin_inf();
+  g.t_kq = mq > 0 ? (double)mk / (double)mq : __builtin_inf();
+  if (alpha < 0) {
+    g.branch = g.rho >= 6.0 && g.t_kq > 3.0 ? 2 : g.rho >= 6.0 && g.t_kq >= 2.0 && g.t_kq <= 3.0 ? 1 : 0;
+    g.alpha = g.branch == 2 ? 0.5 : g.branch == 1 ? 0.25 : 0.0;
+  } else {
+    g.branch = alpha == 0 ? 0 : alpha >= 0.5f ? 2 : 1;
+    g.alpha = alpha;
+  }
+  *reinterpret_cast<CalibGate*>(hist) = g;                // every thread holds its bins by now
+}
+
+// s of each channel: the RMS over the sequences of the per-sequence maxima,
+// s = Kbar^alpha / Qbar^(1-alpha), rounded once to fp32.
+__global__ void __launch_bounds__(64) k_calib_scales(const uint32_t* __restrict__ stats,
+                                                     const CalibGate* __restrict__ gate, int n, int hd,
+                                                     float* __restrict__ s_out) {
+#pragma clang fp contract(off)
+  const int i = blockIdx.x * 64 + threadIdx.x;
+  if (i >= hd) return;
+  const double alpha = gate->alpha;
+  float s32 = 1.0f;
+  if (alpha != 0.0) {
+    double sk = 0.0, sq = 0.0;
+#pragma unroll 4
+    for (int r = 0; r < n; ++r) {
+      const double kv = (double)__uint_as_float(stats[(size_t)(2 * r) * hd + i]);
+      const double qv = (double)__uint_as_float(stats[(size_t)(2 * r + 1) * hd + i]);
+      sk += kv * kv;
+      sq += qv * qv;
+    }
+    const double kbar = sqrt(sk / n), qbar = sqrt(sq / n);
+    const double s = pow(kbar, alpha) / pow(qbar, 1.0 - alpha);
+    const bool bad = kbar == 0 || qbar == 0 || !__builtin_isfinite(s) || s == 0;
+    s32 = bad ? 1.0f : (float)s;
+  }
+  s_out[i] = s32;
+}
+
+// ---------------------------------------------------------------------------
 // Pairs of inputs go through the packed routine the attention kernels use.
 __global__ void k_selftest_exp2(const half_t* __restrict__ x, half_t* __restrict__ y, long n) {
   const long i = 2 * ((long)blockIdx.x * blockDim.x + threadIdx.x);
@@ -659,8 +785,8 @@ hipError_t launch_prep_kv(const half_t* k, const half_t* v, const float* s, cons
   return hipGetLastError();
 }
 
-hipError_t launch_calib(const half_t* q, const half_t* k, int n, int S, int hq, int hkv, int D, uint32_t* stats,
-                        unsigned long long* hist, hipStream_t st) {
+hipError_t launch_calib(const half_t* q, const half_t* k, int n, int S, int hq, int hkv, int D, float alpha,
+                        uint32_t* stats, unsigned long long* hist, float* s_out, hipStream_t st) {
   // stats and hist are adjacent in the workspace (hist follows, rounded up to
   // 256 bytes): one fill clears both
   const size_t words = (size_t)(reinterpret_cast<uint32_t*>(hist) - stats) + 2 * 32768;
@@ -673,6 +799,9 @@ hipError_t launch_calib(const half_t* q, const half_t* k, int n, int S, int hq, 
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   if (e != hipSuccess) return e;
   k_calib<<<dim3((unsigned)((tokens + a.per_wg - 1) / a.per_wg)), dim3(kCalibThreads), lds, st>>>(a);
+  k_calib_gate<<<dim3(1), dim3(kGateThreads), 0, st>>>(stats, hist, n, hkv * D, alpha);
+  k_calib_scales<<<dim3((unsigned)((hkv * D + 63) / 64)), dim3(64), 0, st>>>(
+      stats, reinterpret_cast<const CalibGate*>(hist), n, hkv * D, s_out);
   return hipGetLastError();
 }
 

@@ -85,3 +85,28 @@ def test_calibration(h, n, s, hq, hkv, d):
         assert abs(rep["t_kq"] - want["t_kq"]) <= 1e-9 * want["t_kq"]
         ulps = np.abs(to_np(sg).view(np.int32).astype(np.int64) - sw.view(np.int32).astype(np.int64))
         assert ulps.max() <= 1
+
+
+# the gate's reductions: no positive P99, one value, order statistics on both
+# sides of a bin that another thread holds, more channels than threads
+@pytest.mark.parametrize("kind,n,s,hkv,d", [("zero", 1, 3, 1, 64), ("one_value", 2, 50, 1, 64), ("split99", 1, 100, 1, 64),
+                                            ("split99", 3, 77, 2, 128), ("normal", 40, 5, 10, 256)])
+def test_calibration_gate(h, kind, n, s, hkv, d):
+    rng = np.random.default_rng(n * s + hkv)
+    q, k = _draw(rng, n, s, hkv, d), _draw(rng, n, s, hkv, d)
+    if kind == "zero":
+        k[:] = 0
+    elif kind == "one_value":
+        k[:] = np.float16(-2.5)
+    elif kind == "split99":                       # the largest 1% from 2^-3 up: the two order statistics far apart
+        k[:] = np.float16(0.0625)
+        flat = k.reshape(-1)
+        flat[:(flat.size - 1) // 100] = np.float16(7.0)
+    for alpha in (-1.0, 0.25):
+        sg, rep = h.hifa4_calibrate_smooth_qk(to_gpu(q), to_gpu(k), alpha)
+        sw, want = osmooth.calibrate(q, k, hkv, alpha)
+        assert rep["branch"] == want["branch"] and rep["alpha_used"] == want["alpha_used"]
+        for name in ("rho_k", "t_kq"):            # float64 on both sides, a few roundings
+            assert rep[name] == want[name] or abs(rep[name] - want[name]) <= 1e-12 * want[name], name
+        ulps = np.abs(to_np(sg).view(np.int32).astype(np.int64) - sw.view(np.int32).astype(np.int64))
+        assert ulps.max() <= 1
