@@ -111,31 +111,36 @@ def _check(status: int, what: str):
         raise Hifa4Error(f"{what}: {STATUS.get(status, status)}: {hifa4_last_error()}")
 
 
+_torch_module = None
+
+
 def _torch():
-    import torch
-    return torch
+    global _torch_module
+    if _torch_module is None:
+        import torch
+        _torch_module = torch
+    return _torch_module
 
 
 def _ptr(t) -> Optional[int]:
     return None if t is None else t.data_ptr()
 
 
-def _stream(device=None) -> int:
-    torch = _torch()
-    return torch.cuda.current_stream(device).cuda_stream
+def _stream(device) -> int:
+    # the handle of torch.cuda.current_stream(device) without the Stream object around it
+    return _torch()._C._cuda_getCurrentRawStream(device.index)
 
 
 def _require(t, dtype, name):
-    torch = _torch()
     if t is None:
+        return
+    if t.is_cuda and t.dtype == dtype and t.is_contiguous():
         return
     if not t.is_cuda:
         raise ValueError(f"{name} must be a GPU tensor")
     if t.dtype != dtype:
         raise ValueError(f"{name} must be {dtype}, got {t.dtype}")
-    if not t.is_contiguous():
-        raise ValueError(f"{name} must be contiguous")
-    del torch
+    raise ValueError(f"{name} must be contiguous")
 
 
 @dataclass
@@ -267,10 +272,11 @@ class Workspace:
         self.buf = None
 
     def get(self, nbytes: int, device):
-        torch = _torch()
-        if self.buf is None or self.buf.numel() < nbytes or self.buf.device != device:
-            self.buf = torch.empty(max(nbytes, 256), dtype=torch.uint8, device=device)
-        return self.buf
+        buf = self.buf
+        if buf is None or buf.numel() < nbytes or buf.device != device:
+            torch = _torch()
+            self.buf = buf = torch.empty(max(nbytes, 256), dtype=torch.uint8, device=device)
+        return buf
 
 
 _default_ws = Workspace()
