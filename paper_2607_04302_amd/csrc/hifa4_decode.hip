@@ -42,8 +42,8 @@
 //
 // What bounds it: one step of 8 sequences of 32768 tokens (Hq 32, Hkv 8, D 128)
 // reads 302 MB, 59 us at the 5.1 TB/s that large reads reach on this card, and
-// takes 77 us (89 us before); 32 sequences of 300 to 8192 tokens take 52.6 us
-// (82.5), one of 4096 tokens 18 us (20.6).  Until now codes became int8
+// takes 77 us (89 us before); 32 sequences of 300 to 8192 tokens take 50.5 us
+// (82.5), one of 4096 tokens 15 us (20.6; its kernels 13.9).  Until now codes became int8
 // operands, 9400 VALU instructions a wave for 8 blocks (512 of them
 // quarter-rate multiplies) against 4750 here; VALU issue and the cache stream
 // now overlap at about 65% each.
@@ -723,7 +723,7 @@ __global__ void __launch_bounds__(64 * max_waves(G), (G * RP <= 2 ? 4 : 2)) k_de
 // scan, 64 splits at a time, which also sums l_s R_s); the partial sums,
 // loaded before the scan, are then weighted and added, thread (part,
 // channel) taking every parts-th split, and the parts combined through LDS.
-constexpr int kMergeThreads = 512;
+constexpr int kMergeThreads = 512;              // most per workgroup
 
 __global__ void __launch_bounds__(kMergeThreads) k_decode_merge(DecodeArgs a) {
   extern __shared__ float R[];                    // [n_split], then partial sums, then the l sum
@@ -737,15 +737,15 @@ __global__ void __launch_bounds__(kMergeThreads) k_decode_merge(DecodeArgs a) {
   const int run0 = min(max(a.packed ? a.runbase[b] : b * a.n_split, 0), a.max_runs - 1);
   const int ns = min((nblk + a.bps - 1) / a.bps, a.max_runs - run0);
   const size_t first = (size_t)head * a.max_runs + run0;
-  const int tid = threadIdx.x, lane = tid & 63;
+  const int tid = threadIdx.x, lane = tid & 63, threads = blockDim.x;
   // the runs have read this row's run maxima; clearing them here
   // (a kernel write, so it is part of a captured graph too) means that no word
   // of a finished call can satisfy a later call's wait, whatever its epoch
   if (blockIdx.y == 0)
-    for (int s = tid; s < ns; s += kMergeThreads) a.runmax[first + s] = 0;
+    for (int s = tid; s < ns; s += threads) a.runmax[first + s] = 0;
   const int D = a.D;
   const int CW = D / (int)gridDim.y;              // this workgroup's channels
-  const int parts = kMergeThreads / CW;           // threads per channel
+  const int parts = threads / CW;                 // threads per channel
   float* acc_s = R + a.n_split;                   // [parts][CW]
   float* lsum_s = acc_s + parts * CW;
   const float4* sp = a.spart + first;
@@ -948,9 +948,12 @@ hipError_t launch_decode(const DecodeLaunch& d, hipStream_t st) {
   const long rows = (long)d.batch * d.hq;
   int slices = 1;
   while (rows * slices < kMinWorkgroups && d.D / (2 * slices) >= 32) slices *= 2;
-  const size_t lds3 = ((size_t)a.n_split + kMergeThreads + 1) * sizeof(float);
+  // two or more rows per compute unit: smaller workgroups, so that more rows
+  // overlap their chains of loads (1024 rows: 7.5 us with 512 threads, 5.5 with 256)
+  const int threads = rows >= 512 ? kMergeThreads / 2 : kMergeThreads;
+  const size_t lds3 = ((size_t)a.n_split + threads + 1) * sizeof(float);
   if ((e = allow_lds(k_decode_merge, lds3)) != hipSuccess) return e;
-  k_decode_merge<<<dim3((unsigned)rows, slices), dim3(kMergeThreads), lds3, st>>>(a);
+  k_decode_merge<<<dim3((unsigned)rows, slices), dim3(threads), lds3, st>>>(a);
   return hipGetLastError();
 }
 
