@@ -45,8 +45,8 @@
 // takes 77 us (89 us before); 32 sequences of 300 to 8192 tokens take 50.5 us
 // (82.5), one of 4096 tokens 15 us (20.6; its kernels 13.9).  Until now codes became int8
 // operands, 9400 VALU instructions a wave for 8 blocks (512 of them
-// quarter-rate multiplies) against 4750 here; VALU issue and the cache stream
-// now overlap at about 65% each.
+// quarter-rate multiplies) against 4750 here; the VALU is now busy half of the
+// time and the cache streams at 4.3 TB/s beside it.
 //
 // MFMA operand convention: lane l holds row / column n = l & 15 of A / B and
 // the K slots 32q..32q+31, q = l >> 4; output value i of lane l is row 4q + i,
