@@ -62,6 +62,7 @@
 
 #include "hifa4_device.h"
 #include "hifa4_decode.h"
+#include "hifa4_decode_plan.h"
 #include "hifa4_internal.h"
 #include "hifa4_packed.h"
 
@@ -446,7 +447,7 @@ __global__ void __launch_bounds__(64 * max_waves(G), (G * RP <= 2 ? 4 : 2)) k_de
     const size_t g0 = ((size_t)(w.t0 + 64 * J) * a.hkv + hk) * G;
     const uint8_t* cb = a.kc + g0 * 32;
     const uint8_t* mb = reinterpret_cast<const uint8_t*>(a.km + g0);
-    const uint32_t last = (uint32_t)(w.L - 1 - 64 * J) * krow;  // of the sequence's last token
+    const uint32_t last = last_key_offset(w.L - 64 * J, krow);
     const uint32_t dst = lds0 + slot * Stage<G>::kBytes;
 #pragma unroll
     for (int i = 0; i < 2 * G; ++i) {
