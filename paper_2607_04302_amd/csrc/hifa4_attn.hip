@@ -168,13 +168,15 @@ __device__ __forceinline__ i8_t ld_op6(const uint8_t* rec, int lane) {
 // Column sums of an FP6 E2M3 operand: the MFMA against an all-ones A operand.
 // The ones are FP4 E2M1 (1.0 = 0b0010; four registers where FP6 takes six,
 // at the same rate) and are written here each time: four moves per block cost
-// less than registers held through the block, where they were spilled.
+// less than registers held through the block, where they were spilled.  The
+// moves are the compiler's own, which waits between them and the MFMA (for an
+// inline write it would not); the empty statement keeps them in the block.
 __device__ __forceinline__ f16v_t mfma_ones(const i8_t& B) {
   i8_t ones = {};
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    int w;
-    asm volatile("v_mov_b32 %0, 0x22222222" : "=v"(w));
+    int w = 0x22222222;
+    asm volatile("" : "+v"(w));
     ones[i] = w;
   }
   const f16v_t zero = {};
