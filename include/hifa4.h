@@ -310,6 +310,10 @@ size_t hifa4_decode_workspace_bytes(const hifa4_problem* p);
  *    HIFA4_ERR_UNSUPPORTED; num_heads_q / num_heads_kv must be <= 8 (else
  *    HIFA4_ERR_UNSUPPORTED).
  * workspace: DEVICE, >= hifa4_decode_workspace_bytes(p).  Asynchronous.
+ * total_tokens sizes the launch; a captured call may be replayed after
+ * cu_seqlens have changed in place, also past total_tokens (within max_seqlen
+ * and the caches): every cached token is still taken in, in a launch of the
+ * captured size.
  * The blocks of a sequence are cut into runs (splits), one kernel takes their
  * scores and their partial outputs, and each run waits, with a bounded spin,
  * for the run maxima that the runs before it in the same row

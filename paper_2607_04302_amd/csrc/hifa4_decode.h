@@ -1,6 +1,7 @@
 // Declarations of the decode step, shared by hifa4_decode.hip and the ABI.
 #pragma once
 
+#include "hifa4_decode_plan.h"
 #include "hifa4_internal.h"
 
 namespace hifa4 {
@@ -21,12 +22,11 @@ struct DecodeLaunch {
   uint8_t* ws;
   hipEvent_t* ev;          // optional; ev[1] is recorded before the merge kernel
   int batch, S, NB, hq, hkv, D, norm;
-  long tokens;             // cached tokens (read where cu is set)
+  long tokens;             // cached tokens, for the plan (read where cu is set)
   int test_no_publish;     // testing: no run maxima published, waits give up after 16 polls
   float c;
 };
 
-size_t decode_workspace_bytes(int batch, int hq, int hkv, int D, int NB);
 hipError_t launch_decode(const DecodeLaunch& d, hipStream_t st);
 
 }  // namespace hifa4

@@ -62,30 +62,10 @@
 
 #include "hifa4_device.h"
 #include "hifa4_decode.h"
-#include "hifa4_decode_plan.h"
 #include "hifa4_internal.h"
 #include "hifa4_packed.h"
 
 namespace hifa4 {
-
-// The size callers allocate by, a function of batch, heads and ceil(max_seqlen /
-// 64) alone: n splits of 8, 4 or 2 blocks per row (the longest that gives 256
-// workgroups of eight kv heads, at most 128 per row), for each a partial O, l,
-// factor product and maximum, and 8 bytes per split where those splits fill
-// the chip, else the room of a row's fp16 scores and block maxima.
-size_t decode_workspace_bytes(int batch, int hq, int hkv, int D, int NB) {
-  const long groups = (long)batch * ((hkv + 7) / 8);
-  size_t n = ((size_t)NB + 7) / 8;
-  for (int bps = 4; bps >= 2 && groups * (long)n < 256; bps /= 2) {
-    const size_t m = ((size_t)NB + bps - 1) / bps;
-    if (m > 128) break;
-    n = m;
-  }
-  const size_t rows = (size_t)batch * hq;
-  size_t b = round_up256(rows * n * D * 4) + round_up256(rows * n * 16);
-  if (groups * (long)n >= 256) return b + round_up256(rows * n * 8);
-  return b + round_up256(rows * NB * 128) + round_up256(rows * ((NB + 7) & ~7) * 2);
-}
 
 namespace {
 
@@ -94,13 +74,6 @@ typedef uint32_t u2_t __attribute__((ext_vector_type(2)));
 typedef uint32_t u4_t __attribute__((ext_vector_type(4)));
 typedef unsigned short u16x2_t __attribute__((ext_vector_type(2)));
 typedef short s16x2_t __attribute__((ext_vector_type(2)));
-
-constexpr int kMaxRun = 8;               // blocks per run (the scores of a run stay in registers)
-// kv heads per workgroup: at D = 256 two workgroups of four fill the LDS
-__host__ __device__ constexpr int max_waves(int G) { return G <= 2 ? 8 : 4; }
-constexpr int kMaxSplitsPerRow = 128;
-constexpr int kMinWorkgroups = 256;      // one per compute unit
-constexpr int kMaxPackedBatch = 256;     // sequences whose runs the kernel enumerates itself
 
 __device__ __forceinline__ int dseq_start(const int* cu, int b, int S) { return cu ? cu[b] : b * S; }
 // a length above max_seqlen is outside the contract; clamping it keeps every
@@ -127,6 +100,16 @@ __device__ __forceinline__ h2_t max_row16(h2_t v) {
   return max_dpp<kDppMirror>(v);
 }
 
+// Where the runs leave their results.
+struct RunStore {
+  float* opart;            // [Hq, stride, D]
+  float4* spart;           // [Hq, stride]: l, product of the run's
+                           // rescale factors, running max after its last block
+  uint64_t* runmax;        // [Hq, stride] run maxima, epoch-tagged; the merge
+                           // kernel clears each row's words after the runs
+  int stride;              // runs of a query head
+};
+
 struct DecodeArgs {
   const half_t* q;         // raw decode queries [batch, Hq, D] fp16
   const float* s;          // smoothing scales [Hkv, D] or null
@@ -135,20 +118,17 @@ struct DecodeArgs {
   const uint8_t* vc;       // canonical V^ cache [batch, NB, Hkv, D, 32]
   const uint32_t* vm;      // [batch, NB, Hkv, D]
   const int* cu;
-  float* opart;            // [Hq, max_runs, D]
-  float4* spart;           // [Hq, max_runs]: l, product of the run's
-                           // rescale factors, running max after its last block
-  uint64_t* runmax;        // [Hq, max_runs] run maxima, epoch-tagged; the merge
-                           // kernel clears each row's words after the runs
-  int* runbase;            // packed runs: [batch] first run of each sequence
+  RunStore usual, grown;   // in the workspace; `grown`: of runs that outgrew the grid
+  int* runbase;            // packed runs: [batch] first run of each sequence (`usual`)
   half_t* o;               // [batch, Hq, D]
   float* lse;              // [Hq, batch]
   uint8_t* dbg_codes;      // [Hq, batch, NB, 32] or null
   uint32_t* dbg_meta;      // [Hq, batch, NB]
-  int batch, S, NB, hq, hkv, D, waves, bps;
+  int batch, S, NB, hq, hkv, D, waves;
+  int bps;                 // blocks per run
   int n_split;             // ceil(NB / bps)
   int packed;              // runs are numbered over the sequences' own lengths
-  int max_runs;            // runs of the grid
+  int tokens;              // cached tokens that the grid of packed runs covers
   float c;
   uint32_t epoch;          // this call's tag (never 0)
   int spin_limit;          // polls before a look-back wait gives up
@@ -161,42 +141,89 @@ struct WaveSpan {
   int hk, b, L, J0, nb, t0, grp, part, run;
 };
 
-// Sequence and part of run blockIdx.x; false when the wave has nothing to do.
+// Bounds of the sequences 64 k + lane of a packed call (empty past the batch).
+constexpr int kScanSteps = kMaxPackedBatch / 64;
+struct Bounds {
+  int first[kScanSteps], end[kScanSteps];
+};
+__device__ __forceinline__ Bounds load_bounds(const DecodeArgs& a, int lane) {
+  Bounds s;
+#pragma unroll
+  for (int k = 0; k < kScanSteps; ++k) {
+    const int b = 64 * k + lane;
+    s.first[k] = s.end[k] = 0;
+    if (64 * k < a.batch && b < a.batch) {
+      s.first[k] = a.cu[b];
+      s.end[k] = a.cu[b + 1];
+    }
+  }
+  return s;
+}
+__device__ __forceinline__ int runs_of(int len, int bps) {
+  return len > 0 ? (((len + 63) >> 6) + bps - 1) / bps : 0;
+}
+// Runs of the sequences before b.
+__device__ __forceinline__ int runs_before(const DecodeArgs& a, const Bounds& s, int lane, int b, int bps) {
+  int n = 0;
+#pragma unroll
+  for (int k = 0; k < kScanSteps; ++k)
+    n += 64 * k + lane < b ? runs_of(min(s.end[k] - s.first[k], a.S), bps) : 0;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) n += __shfl_xor(n, o);
+  return __builtin_amdgcn_readfirstlane(n);
+}
+// Blocks per run of a call whose lengths have grown: the fewest from the plan's
+// on with which all runs fit the workspace (those of kMaxRun blocks always do).
+__device__ __forceinline__ int grown_run_length(const DecodeArgs& a, const Bounds& s, int lane) {
+  int bps = a.bps;
+  while (bps < kMaxRun && runs_before(a, s, lane, a.batch, bps) > a.grown.stride) ++bps;
+  return bps;
+}
+
+enum Span { kRun, kIdle, kGrown };
+
+// Sequence and part of run `run`; kIdle when the wave has nothing to do in it.
 // Packed: the runs are numbered densely over the sequences' own lengths, so
 // the grid holds (nearly) no idle workgroup and the run length can be chosen
 // from the number of cached tokens and not from the longest sequence; every
 // wave finds its sequence by a prefix sum over the batch (one load latency and
 // a scan over 64 lanes).
-__device__ __forceinline__ bool wave_span(const DecodeArgs& a, WaveSpan& w) {
-  w.hk = __builtin_amdgcn_readfirstlane((int)blockIdx.y * a.waves + (int)(threadIdx.x >> 6));
-  if (w.hk >= a.hkv) return false;
+//
+// The grid is that of total_tokens cached tokens, and a captured launch may be
+// replayed over lengths that have grown past it since.  That gives kGrown; with
+// GROWN the run length is settled anew, for a loop in which a workgroup takes
+// several runs.  (Settled in every call it took 0.3 to 0.8 us of 18 to 44.)
+template <bool GROWN>
+__device__ __forceinline__ Span wave_span(const DecodeArgs& a, int run, int tid, WaveSpan& w) {
+  w.hk = __builtin_amdgcn_readfirstlane((int)blockIdx.y * a.waves + (tid >> 6));
+  if (w.hk >= a.hkv) return kIdle;
   w.grp = a.hq / a.hkv;
-  w.run = blockIdx.x;
+  w.run = run;
+  int bps = a.bps;
   if (!a.packed) {
     w.b = w.run / a.n_split;
     w.part = w.run - w.b * a.n_split;
     w.L = dseq_len(a.cu, w.b, a.S);
     w.t0 = dseq_start(a.cu, w.b, a.S);
   } else {
-    const int lane = threadIdx.x & 63;
-    constexpr int kSteps = kMaxPackedBatch / 64;
-    int c0[kSteps], c1[kSteps];
+    const int lane = tid & 63;
+    const Bounds s = load_bounds(a, lane);
+    if (GROWN) {
+      bps = grown_run_length(a, s, lane);
+    } else {
 #pragma unroll
-    for (int k = 0; k < kSteps; ++k) {
-      const int b = 64 * k + lane;
-      c0[k] = c1[k] = 0;
-      if (64 * k < a.batch && b < a.batch) {
-        c0[k] = a.cu[b];
-        c1[k] = a.cu[b + 1];
-      }
+      for (int k = 0; k < kScanSteps; ++k)
+        if ((a.batch - 1) / 64 == k &&
+            __builtin_expect(__builtin_amdgcn_readlane(s.end[k], (a.batch - 1) & 63) > a.tokens, 0))
+          return kGrown;
     }
     int before = 0;                      // runs of the sequences of earlier steps
     bool found = false;
 #pragma unroll
-    for (int k = 0; k < kSteps; ++k) {
+    for (int k = 0; k < kScanSteps; ++k) {
       if (found || 64 * k >= a.batch) break;
-      const int len = min(c1[k] - c0[k], a.S);
-      const int nr = len > 0 ? (((len + 63) >> 6) + a.bps - 1) / a.bps : 0;
+      const int len = min(s.end[k] - s.first[k], a.S);
+      const int nr = runs_of(len, bps);
       int incl = nr;
 #pragma unroll
       for (int o = 1; o < 64; o <<= 1) {
@@ -208,21 +235,21 @@ __device__ __forceinline__ bool wave_span(const DecodeArgs& a, WaveSpan& w) {
         const int j = __builtin_ctzll(over);
         w.b = 64 * k + j;
         w.part = w.run - (before + __builtin_amdgcn_readlane(incl - nr, j));
-        w.t0 = __builtin_amdgcn_readlane(c0[k], j);
+        w.t0 = __builtin_amdgcn_readlane(s.first[k], j);
         w.L = __builtin_amdgcn_readlane(len, j);
         found = true;
       } else {
         before += __builtin_amdgcn_readlane(incl, 63);
       }
     }
-    if (!found) return false;
-    if (w.part == 0 && w.hk == 0 && lane == 0) a.runbase[w.b] = w.run;
+    if (!found) return kIdle;
+    if (!GROWN && w.part == 0 && w.hk == 0 && lane == 0) a.runbase[w.b] = w.run;
   }
   const int nblk = (w.L + 63) >> 6;
-  w.J0 = w.part * a.bps;
-  if (w.J0 >= nblk) return false;
-  w.nb = min(a.bps, nblk - w.J0);
-  return true;
+  w.J0 = w.part * bps;
+  if (w.J0 >= nblk) return kIdle;
+  w.nb = min(bps, nblk - w.J0);
+  return kRun;
 }
 
 // One block's codes and metadata of one kv head in LDS, as the loads lay them
@@ -353,8 +380,7 @@ struct WaveLds {
 constexpr int kLookBatch = 4;                    // run maxima per lane per round
 constexpr int kSpinLimit = 1 << 20;
 
-__device__ __forceinline__ float look_back(const DecodeArgs& a, const uint64_t* f, int part, bool& lost) {
-  const int kq = threadIdx.x & 15;
+__device__ __forceinline__ float look_back(const DecodeArgs& a, const uint64_t* f, int part, int kq, bool& lost) {
   float mm = -__builtin_inff();
   lost = false;
   for (int q0 = 0; q0 < part; q0 += 16 * kLookBatch) {
@@ -409,14 +435,14 @@ __device__ __forceinline__ float look_back(const DecodeArgs& a, const uint64_t* 
 // l is summed per lane and over the row's lanes at the end of the run.
 // PV: B = 16 channels of the block's V^ groups;
 // O[row][ch] = fma(O, r_row, dot * b_V * b_P/16).
-template <int G, int RP, int NORM, bool DEBUG>
-__global__ void __launch_bounds__(64 * max_waves(G), (G * RP <= 2 ? 4 : 2)) k_decode_runs(DecodeArgs a) {
-  __shared__ __align__(16) WaveLds<G, RP> lds[max_waves(G)];
+template <int G, int RP, int NORM, bool DEBUG, bool GROWN>
+__device__ __forceinline__ Span decode_run(const DecodeArgs& a, WaveLds<G, RP>* lds, int run, int tid) {
   WaveSpan w;
-  if (!wave_span(a, w)) return;
+  if (const Span sp = wave_span<GROWN>(a, run, tid, w); sp != kRun) return sp;
   constexpr int D = 64 * G, NT = 4 * G;
-  WaveLds<G, RP>& sl = lds[__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6))];
-  const int lane = threadIdx.x & 63, n = lane & 15, q = lane >> 4, kq = n;
+  const RunStore& rs = GROWN ? a.grown : a.usual;
+  WaveLds<G, RP>& sl = lds[__builtin_amdgcn_readfirstlane(tid >> 6)];
+  const int lane = tid & 63, n = lane & 15, q = lane >> 4, kq = n;
   const int hk = w.hk, nb = w.nb, grp = w.grp;
   const int h0 = hk * grp;                        // first query head of the group
   const size_t row0 = (size_t)w.b * a.hq + h0;
@@ -601,7 +627,7 @@ __global__ void __launch_bounds__(64 * max_waves(G), (G * RP <= 2 ? 4 : 2)) k_de
     const h2_t rm = max_row16(hmax_halves(rmax[p]));
     if (a.publish && kq == 0 && 4 * p + q < grp) {
       const uint64_t word = ((uint64_t)a.epoch << 32) | (uint64_t)__builtin_bit_cast(uint16_t, rm[0]);
-      __hip_atomic_store(a.runmax + (size_t)(h0 + 4 * p + q) * a.max_runs + w.run, word, __ATOMIC_RELAXED,
+      __hip_atomic_store(rs.runmax + (size_t)(h0 + 4 * p + q) * rs.stride + w.run, word, __ATOMIC_RELAXED,
                          __HIP_MEMORY_SCOPE_AGENT);
     }
     l[p] = 0.0f;
@@ -610,7 +636,7 @@ __global__ void __launch_bounds__(64 * max_waves(G), (G * RP <= 2 ? 4 : 2)) k_de
 #pragma unroll
   for (int p = 0; p < RP; ++p) {
     bool lp = false;
-    float mm = look_back(a, a.runmax + (size_t)(h0 + prow[p]) * a.max_runs + (w.run - w.part), w.part, lp);
+    float mm = look_back(a, rs.runmax + (size_t)(h0 + prow[p]) * rs.stride + (w.run - w.part), w.part, kq, lp);
     int lf = lp ? 1 : 0;
 #pragma unroll
     for (int o = 1; o < 16; o <<= 1) {
@@ -706,13 +732,27 @@ __global__ void __launch_bounds__(64 * max_waves(G), (G * RP <= 2 ? 4 : 2)) k_de
     for (int o = 1; o < 16; o <<= 1) ls += __shfl_xor(ls, o);
     const int r = 4 * p + q;
     if (r < grp) {
-      const size_t e = (size_t)(h0 + r) * a.max_runs + w.run;
-      float* dst = a.opart + e * D + n;
+      const size_t e = (size_t)(h0 + r) * rs.stride + w.run;
+      float* dst = rs.opart + e * D + n;
 #pragma unroll
       for (int t = 0; t < NT; ++t) dst[16 * t] = O[t][p];
-      if (kq == 0) a.spart[e] = make_float4(lost[p] ? __builtin_nanf("") : ls, prod[p], (float)m[p], 0.0f);
+      if (kq == 0) rs.spart[e] = make_float4(lost[p] ? __builtin_nanf("") : ls, prod[p], (float)m[p], 0.0f);
     }
   }
+  return kRun;
+}
+
+template <int G, int RP, int NORM, bool DEBUG>
+__global__ void __launch_bounds__(64 * max_waves(G), (G * RP <= 2 ? 4 : 2)) k_decode_runs(DecodeArgs a) {
+  __shared__ __align__(16) WaveLds<G, RP> lds[max_waves(G)];
+  if (__builtin_expect(decode_run<G, RP, NORM, DEBUG, false>(a, lds, blockIdx.x, threadIdx.x) != kGrown, 1)) return;
+  // a copy of its own: a loop around the only one holds what the runs share in
+  // registers, which cost every call 0.8 us
+  int run = blockIdx.x, tid;
+  do {
+    tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));         // (and so that this loop holds little)
+  } while (decode_run<G, RP, NORM, DEBUG, true>(a, lds, run, tid) == kRun && (run += gridDim.x, true));
 }
 
 // ---------------------------------------------------------------------------
@@ -730,31 +770,44 @@ __global__ void __launch_bounds__(kMergeThreads) k_decode_merge(DecodeArgs a) {
   extern __shared__ float R[];                    // [n_split], then partial sums, then the l sum
   const int row = blockIdx.x;                     // b * hq + head
   const int b = row / a.hq, head = row % a.hq;
-  const int L = dseq_len(a.cu, b, a.S);
+  // the sequence's runs [run0, run0 + ns)
+  int run0 = b * a.n_split, bps = a.bps, L = a.S;
+  RunStore st = a.usual;
+  if (a.packed) {
+    int first = a.cu[b], next = a.cu[b + 1], end = a.cu[a.batch];
+    run0 = a.runbase[b];
+    asm volatile("" : "+s"(first), "+s"(next), "+s"(end), "+s"(run0));      // the loads side by side
+    L = min(next - first, a.S);
+    if (__builtin_expect(end > a.tokens, 0)) {
+      const Bounds s = load_bounds(a, threadIdx.x & 63);
+      bps = grown_run_length(a, s, threadIdx.x & 63);
+      run0 = runs_before(a, s, threadIdx.x & 63, b, bps);
+      st = a.grown;
+    }
+  } else {
+    L = dseq_len(a.cu, b, a.S);
+  }
   const int nblk = (L + 63) >> 6;
-  if (nblk == 0) return;
-  // the sequence's runs [run0, run0 + ns) (kept inside the workspace where
-  // cu_seqlens holds more tokens than the problem names)
-  const int run0 = min(max(a.packed ? a.runbase[b] : b * a.n_split, 0), a.max_runs - 1);
-  const int ns = min((nblk + a.bps - 1) / a.bps, a.max_runs - run0);
-  const size_t first = (size_t)head * a.max_runs + run0;
+  if (nblk <= 0) return;
+  const int ns = (nblk + bps - 1) / bps;
+  const size_t first = (size_t)head * st.stride + run0;
   const int tid = threadIdx.x, lane = tid & 63, threads = blockDim.x;
   // the runs have read this row's run maxima; clearing them here
   // (a kernel write, so it is part of a captured graph too) means that no word
   // of a finished call can satisfy a later call's wait, whatever its epoch
   if (blockIdx.y == 0)
-    for (int s = tid; s < ns; s += threads) a.runmax[first + s] = 0;
+    for (int s = tid; s < ns; s += threads) st.runmax[first + s] = 0;
   const int D = a.D;
   const int CW = D / (int)gridDim.y;              // this workgroup's channels
   const int parts = threads / CW;                 // threads per channel
   float* acc_s = R + a.n_split;                   // [parts][CW]
   float* lsum_s = acc_s + parts * CW;
-  const float4* sp = a.spart + first;
+  const float4* sp = st.spart + first;
   // the partial sums do not depend on the scan: load them first
   const int c = tid % CW, part = tid / CW, ch = (int)blockIdx.y * CW + c;
   constexpr int kMaxHeld = 16;
   float po[kMaxHeld];
-  const float* op = a.opart + first * D + ch;
+  const float* op = st.opart + first * D + ch;
 #pragma unroll
   for (int k = 0; k < kMaxHeld; ++k) {
     const int s = part + k * parts;
@@ -803,61 +856,6 @@ __global__ void __launch_bounds__(kMergeThreads) k_decode_merge(DecodeArgs a) {
   }
 }
 
-// Run length, workgroup shape and grid of a call.  The longest useful run is
-// the one with which every wave of the call is resident at once (one round of
-// waves, 16 or 8 per compute unit as the registers and the LDS allow); shorter
-// runs would only add partial outputs, longer ones leave the chip idle.  At
-// least ceil(NB/128) blocks, since every split of a row adds to its look-back
-// and merge, and at most 8, which is what the registers of a wave hold; and as
-// many as it takes for the partials to fit the workspace.  The workgroup takes
-// fewer waves where eight per workgroup would leave compute units empty.
-struct DecodePlan {
-  int waves, bps, packed;
-  long runs;               // runs of the grid
-};
-
-void decode_offsets(int batch, int hq, int D, const DecodePlan& pl, size_t off[5]) {
-  const size_t n = (size_t)hq * (size_t)pl.runs;
-  size_t o = 0;
-  off[0] = o; o += round_up256(n * D * 4);                             // partial O
-  off[1] = o; o += round_up256(n * 16);                                // l, factor product, max
-  off[2] = o; o += round_up256(n * 8);                                 // run maxima
-  off[3] = o; o += pl.packed ? round_up256((size_t)batch * 4) : 0;     // first run of each sequence
-  off[4] = o;
-}
-
-// tokens: the cached tokens of a THD problem, or -1 (every length is max_seqlen).
-DecodePlan plan_decode(int batch, int hq, int hkv, int D, int NB, long tokens) {
-  const int waves_per_cu = (D / 64) * (hq / hkv > 4 ? 2 : 1) <= 2 ? 16 : 8;
-  long slots = (long)kMinWorkgroups * waves_per_cu / hkv;              // runs resident at once
-  if (slots < 1) slots = 1;
-  const size_t room = decode_workspace_bytes(batch, hq, hkv, D, NB);
-  DecodePlan p;
-  const bool pack = tokens >= 0 && batch <= kMaxPackedBatch;
-  long blocks = (long)batch * NB;
-  if (pack && tokens / 64 + batch < blocks) blocks = tokens / 64 + batch;
-  long bps = (blocks + slots - 1) / slots;
-  const long least = (NB + kMaxSplitsPerRow - 1) / kMaxSplitsPerRow;
-  if (bps < least) bps = least;
-  if (bps > kMaxRun) bps = kMaxRun;
-  for (;; ++bps) {
-    p.bps = (int)bps;
-    p.packed = pack;
-    p.runs = (long)batch * ((NB + bps - 1) / bps);
-    if (pack && tokens / (64 * bps) + batch < p.runs) p.runs = tokens / (64 * bps) + batch;
-    size_t off[5];
-    decode_offsets(batch, hq, D, p, off);
-    if (off[4] <= room) break;
-    if (bps < kMaxRun) continue;
-    p.packed = 0;                        // always fits: the workspace holds ceil(NB/8) runs of every sequence
-    p.runs = (long)batch * ((NB + bps - 1) / bps);
-    break;
-  }
-  p.waves = hkv < max_waves(D / 64) ? hkv : max_waves(D / 64);
-  while (p.waves > 1 && p.runs * ((hkv + p.waves - 1) / p.waves) < kMinWorkgroups) p.waves = (p.waves + 1) / 2;
-  return p;
-}
-
 // Epoch tags of the run maxima: a fresh value per call, starting from a
 // random point.  Tags only separate eager calls; under graph replay the tag
 // is the captured one, and what keeps a replay from reading the previous
@@ -898,9 +896,13 @@ void launch_runs(const DecodeArgs& a, int grp, int norm, bool debug, dim3 grid, 
 
 hipError_t launch_decode(const DecodeLaunch& d, hipStream_t st) {
   const DecodePlan pl = plan_decode(d.batch, d.hq, d.hkv, d.D, d.NB, d.cu ? d.tokens : -1);
-  size_t off[5];
-  decode_offsets(d.batch, d.hq, d.D, pl, off);
   uint8_t* ws = d.ws;
+  const auto store = [&](long runs) {
+    size_t off[4];
+    decode_offsets(d.batch, d.hq, d.D, runs, pl.words(), 0, off);
+    return RunStore{reinterpret_cast<float*>(ws + off[1]), reinterpret_cast<float4*>(ws + off[2]),
+                    reinterpret_cast<uint64_t*>(ws + off[0]), (int)runs};
+  };
   DecodeArgs a;
   a.q = d.q;
   a.s = d.s;
@@ -909,9 +911,10 @@ hipError_t launch_decode(const DecodeLaunch& d, hipStream_t st) {
   a.vc = d.vc;
   a.vm = d.vm;
   a.cu = d.cu;
-  a.opart = reinterpret_cast<float*>(ws + off[0]);
-  a.spart = reinterpret_cast<float4*>(ws + off[1]);
-  a.runmax = reinterpret_cast<uint64_t*>(ws + off[2]);
+  a.usual = store(pl.runs);
+  a.grown = pl.packed ? store(pl.longest) : a.usual;
+  size_t off[4];
+  decode_offsets(d.batch, d.hq, d.D, pl.runs, pl.words(), pl.packed, off);
   a.runbase = reinterpret_cast<int*>(ws + off[3]);
   a.epoch = next_epoch();
   a.spin_limit = d.test_no_publish ? 16 : kSpinLimit;
@@ -929,7 +932,7 @@ hipError_t launch_decode(const DecodeLaunch& d, hipStream_t st) {
   a.bps = pl.bps;
   a.n_split = (d.NB + pl.bps - 1) / pl.bps;
   a.packed = pl.packed;
-  a.max_runs = (int)pl.runs;
+  a.tokens = (int)d.tokens;
   a.waves = pl.waves;
   a.c = d.c;
   const int grp = d.hq / d.hkv;

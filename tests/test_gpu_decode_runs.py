@@ -9,7 +9,8 @@ import pytest
 
 from paper_2607_04302_amd.workloads import small_case
 
-from test_gpu_decode import _decode_and_compare, _say, h  # noqa: F401  (h: the library fixture)
+from _gpu_util import check_close, to_gpu, to_np
+from test_gpu_decode import _build_cache, _decode_and_compare, _say, h  # noqa: F401  (h: the library fixture)
 
 pytestmark = pytest.mark.gpu
 
@@ -47,3 +48,44 @@ def test_decode_max_seqlen_above_every_length(h, norm):  # noqa: F811
     qd = np.random.default_rng(45).standard_normal((len(lens), 8, 128)).astype(np.float16)
     _say("decode bound above lengths", norm)
     _decode_and_compare(h, qd, k, v, cu, None, 5000, norm=norm)
+
+
+@pytest.mark.parametrize("captured,grown,d,hq,hkv", [
+    ((64, 1, 30), (1500, 64, 2000), 128, 8, 2),              # runs of 1 or 2, several per workgroup
+    ((1, 1), (9000, 8191), 64, 8, 8),                        # runs lengthened until they fit the workspace
+    ((200,) * 70, (700,) * 35 + (65,) * 35, 64, 2, 1),       # two steps of the prefix sum
+    ((5, 0, 3), (300, 1200, 0), 256, 8, 1),                  # two rows per lane; a sequence appears, another empties
+])
+def test_decode_captured_lengths_grow(h, captured, grown, d, hq, hkv):  # noqa: F811
+    """A captured step replayed over lengths that have grown in place past the
+    captured number of tokens, within max_seqlen: every run is computed, P^
+    equals the eager call on the new lengths bit for bit, O and LSE agree to
+    fp32 rounding (the runs may be cut elsewhere)."""
+    import torch
+    cap = max(grown)
+    _, k, v, cu = small_case(heads_q=hkv, heads_kv=hkv, head_dim=d, seqlens=grown, seed=51)
+    qd = to_gpu(np.random.default_rng(52).standard_normal((len(grown), hq, d)).astype(np.float16))
+    kc, km, vc, vm, cu_new = _build_cache(h, k, v, None, cu, cap)
+    want = h.hifa4_decode_fwd(qd, kc, km, vc, vm, cu_seqlens=cu_new, max_seqlen=cap, debug_p=True)
+    cu_t = to_gpu(np.concatenate([[0], np.cumsum(captured)]).astype(np.int32))
+    t = int(sum(captured))
+    kw = dict(cu_seqlens=cu_t, max_seqlen=cap, workspace=h.Workspace(), debug_p=True)
+    _say("decode captured lengths grow", len(grown), t, sum(grown), d)
+    h.hifa4_decode_fwd(qd, kc[:t], km[:t], vc, vm, **kw)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        got = h.hifa4_decode_fwd(qd, kc[:t], km[:t], vc, vm, **kw)
+    for step in range(3):
+        cu_t.copy_(cu_new)
+        for x in got:
+            x.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        live = [b for b, n in enumerate(grown) if n]
+        assert torch.equal(got[2], want[2]) and torch.equal(got[3], want[3]), step
+        # two roundings of fp16 outputs apart; LSE: a few fp32 roundings of values below 2^5
+        check_close(to_np(got[0][live]), to_np(want[0][live]), atol=1e-4, rtol=2e-3, what="O")
+        check_close(to_np(got[1][:, live]), to_np(want[1][:, live]), atol=2e-5, rtol=0, what="LSE")
+        h.hifa4_decode_fwd(qd, kc, km, vc, vm, cu_seqlens=cu_new, max_seqlen=cap)      # eager work between
+        torch.cuda.synchronize()
