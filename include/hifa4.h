@@ -319,12 +319,15 @@ size_t hifa4_decode_workspace_bytes(const hifa4_problem* p);
  * for the run maxima that the runs before it in the same row
  * publish (tagged with a per-call value; the last kernel of the call clears
  * them, so no word of an earlier call, eager or replayed from a graph,
- * satisfies a wait).  The waits end because every GPU engine dispatches the
- * workgroups of a grid in index order and each waits only on lower indices;
- * if a wait nevertheless gives up, that row's o and lse are NaN (never a
- * silently wrong value).  opt->test_decode_no_publish != 0 (testing only)
- * publishes nothing and lets every wait give up after 16 polls, so that the
- * rows of every split after the first come out NaN. */
+ * satisfies a wait).  Every GPU engine dispatches the workgroups of a grid in
+ * index order and each waits only on lower indices, so the waits are short
+ * where the call has the GPU to itself; next to other work (a second decode
+ * call on another stream whose waiting workgroups hold this one's off the GPU)
+ * a wait may run to its limit, some milliseconds, and the run then scores the
+ * earlier blocks of its sequence itself: the results are the same bits.
+ * opt->test_decode_no_publish (testing only): 2 publishes nothing and lets
+ * every wait give up after 16 polls; with 1 the rows that waited come out NaN
+ * instead of being computed. */
 hifa4_status hifa4_decode_fwd(const hifa4_problem* p, const hifa4_fwd_options* opt,
                               const void* q, const void* k_codes, const void* k_meta,
                               const void* v_codes, const void* v_meta, const float* s,

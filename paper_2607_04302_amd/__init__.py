@@ -378,7 +378,7 @@ def hifa4_decode_workspace_bytes(shape: Shape) -> int:
 def hifa4_decode_fwd(q, k_codes, k_meta, v_codes, v_meta, s=None, cu_seqlens=None, max_seqlen=None,
                      norm: int = NORM_PREORDER, smooth_qk: Optional[bool] = None, debug_p: bool = False,
                      out=None, lse=None, workspace: Optional[Workspace] = None, timing_events=None,
-                     test_no_publish: bool = False):
+                     test_no_publish: int = 0):
     """One decode step over a packed HIF4 cache: q [B, Hq, D] fp16 is the query
     of each sequence's newest token; the cache is the output of
     hifa4_quantize_qk (K^, same s) and hifa4_quantize_v (V^) over the cached
@@ -414,7 +414,7 @@ def hifa4_decode_fwd(q, k_codes, k_meta, v_codes, v_meta, s=None, cu_seqlens=Non
         ev_arr = (ctypes.c_void_p * 3)(*[e.cuda_event for e in timing_events])
     opt = FwdOptions(norm, OPERANDS_HIF4, 1 if smooth_qk else 0, _ptr(pc), _ptr(pm),
                      ctypes.cast(ev_arr, ctypes.c_void_p) if ev_arr is not None else None, 0,
-                     1 if test_no_publish else 0)
+                     int(test_no_publish))
     p = sh.problem()
     need = int(lib.hifa4_decode_workspace_bytes(ctypes.byref(p)))
     ws = (workspace or _default_ws).get(need, dev)

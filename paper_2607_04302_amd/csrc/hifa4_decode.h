@@ -24,6 +24,7 @@ struct DecodeLaunch {
   int batch, S, NB, hq, hkv, D, norm;
   long tokens;             // cached tokens, for the plan (read where cu is set)
   int test_no_publish;     // testing: no run maxima published, waits give up after 16 polls
+                           // (1: rows that waited come out NaN, 2: as without publishing)
   float c;
 };
 

@@ -131,7 +131,8 @@ struct DecodeArgs {
   int tokens;              // cached tokens that the grid of packed runs covers
   float c;
   uint32_t epoch;          // this call's tag (never 0)
-  int spin_limit;          // polls before a look-back wait gives up
+  int spin_limit;          // polls before a look-back gives up
+  int rescore;             // 0: a row whose look-back gave up comes out NaN (testing)
   int publish;             // 0: no run maxima are published (testing the give-up)
 };
 
@@ -374,14 +375,15 @@ struct WaveLds {
 // The running maximum entering run w.part of a softmax row: the maximum of the
 // earlier runs' epoch-tagged maxima of the sequence (f: the row's word of the
 // sequence's first run), 16 lanes per row, kLookBatch words each per round,
-// every load of a round in flight before the first is checked.  A spin limit
-// ends every wait; a wait that gives up sets `lost` (the run then poisons its
-// partial, so the row's O and LSE come out NaN instead of silently wrong).
+// every load of a round in flight before the first is checked.  A limit on the
+// polls of a look-back (some milliseconds) ends every wait; one that gives up
+// sets `lost`, and the wave takes the missing maximum from the scores itself.
 constexpr int kLookBatch = 4;                    // run maxima per lane per round
-constexpr int kSpinLimit = 1 << 20;
+constexpr int kSpinLimit = 4096;
 
 __device__ __forceinline__ float look_back(const DecodeArgs& a, const uint64_t* f, int part, int kq, bool& lost) {
   float mm = -__builtin_inff();
+  int polls = a.spin_limit;
   lost = false;
   for (int q0 = 0; q0 < part; q0 += 16 * kLookBatch) {
     uint64_t wd[kLookBatch];
@@ -395,7 +397,7 @@ __device__ __forceinline__ float look_back(const DecodeArgs& a, const uint64_t* 
       const int q = q0 + 16 * k + kq;
       if (q < part) {
         uint64_t v = wd[k];
-        for (int it = 0; (uint32_t)(v >> 32) != a.epoch && it < a.spin_limit; ++it) {
+        for (; (uint32_t)(v >> 32) != a.epoch && polls > 0; --polls) {
           __builtin_amdgcn_s_sleep(2);
           v = __hip_atomic_load(f + q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
@@ -410,8 +412,11 @@ __device__ __forceinline__ float look_back(const DecodeArgs& a, const uint64_t* 
 // ---------------------------------------------------------------------------
 // 1. Runs.  Wave = kv head, workgroup = (run, kv heads).  A wave never meets a
 // barrier.  The earlier runs of a sequence belong to workgroups with lower
-// indices, which each XCD dispatches first, so the lowest unfinished workgroup
-// is always running; a spin limit still ends every wait.
+// indices, which each XCD dispatches first, so in a call that has the GPU to
+// itself the lowest unfinished workgroup is always running and the waits are
+// short.  No result depends on that: two calls on two streams can hold each
+// other's lower workgroups off the GPU with workgroups that wait.  A wait that
+// runs to its limit ends in the wave scoring the earlier blocks itself.
 //
 // The run's block loads (K of each block, then V of each block) form one
 // stream through two LDS buffers of the wave, filled by asynchronous copies
@@ -548,13 +553,16 @@ __device__ __forceinline__ Span decode_run(const DecodeArgs& a, WaveLds<G, RP>* 
   // A operands of A row n (zero where it holds no query row)
   const int arow = 4 * (n & 3) + (n >> 2);
   const bool alive = (n & 3) < RP && arow < grp;
-  AOperand qa[G];
+  auto q_operands = [&](AOperand (&qa)[G]) {
 #pragma unroll
-  for (int g = 0; g < G; ++g) {
-    u4_t d = {0, 0, 0, 0};
-    if (alive) d = *reinterpret_cast<const u4_t*>(&sl.a[(arow * G + g) * 16 + 4 * q]);
-    qa[g] = a_operand(d);
-  }
+    for (int g = 0; g < G; ++g) {
+      u4_t d = {0, 0, 0, 0};
+      if (alive) d = *reinterpret_cast<const u4_t*>(&sl.a[(arow * G + g) * 16 + 4 * q]);
+      qa[g] = a_operand(d);
+    }
+  };
+  AOperand qa[G];
+  q_operands(qa);
 
   // --- scores ---
   // sc: the scores of the run's blocks (the lane's four keys per pass), a
@@ -580,11 +588,8 @@ __device__ __forceinline__ Span decode_run(const DecodeArgs& a, WaveLds<G, RP>* 
   uint32_t boff;
   asm("s_mov_b32 %0, 0x30000000" : "=s"(boff));
   const int clane = n * (32 * G) + 8 * q, mlane = Stage<G>::kCodes + n * (4 * G);
-  for (int j = 0; j < nb; ++j) {
-    const uint8_t* blk = &sl.buf[j & 1][0];
-    const int left = w.L - 64 * (w.J0 + j);       // keys of the block and after
-    arrived(j);
-    float acc[4][RP];
+  // scores of a block in LDS: acc[t][p] the lane's key 4n + t of its row in pass p
+  auto score = [&](const AOperand (&qa)[G], const uint8_t* blk, float (&acc)[4][RP]) {
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
 #pragma unroll
@@ -601,6 +606,12 @@ __device__ __forceinline__ Span decode_run(const DecodeArgs& a, WaveLds<G, RP>* 
       }
     }
     wait_lds();
+  };
+  for (int j = 0; j < nb; ++j) {
+    const int left = w.L - 64 * (w.J0 + j);       // keys of the block and after
+    arrived(j);
+    float acc[4][RP];
+    score(qa, &sl.buf[j & 1][0], acc);
     if (j + 2 < 2 * nb) fetch(j + 2);            // a run of one block has two items only
     shift();
 #pragma unroll
@@ -622,6 +633,7 @@ __device__ __forceinline__ Span decode_run(const DecodeArgs& a, WaveLds<G, RP>* 
   half_t m[RP];
   float l[RP], prod[RP];
   bool lost[RP];
+  int any_lost = 0;
 #pragma unroll
   for (int p = 0; p < RP; ++p) {
     const h2_t rm = max_row16(hmax_halves(rmax[p]));
@@ -645,6 +657,34 @@ __device__ __forceinline__ Span decode_run(const DecodeArgs& a, WaveLds<G, RP>* 
     }
     m[p] = (half_t)mm;
     lost[p] = lf != 0;
+    any_lost |= lf;
+  }
+  if (__builtin_expect(a.rescore && __ballot(any_lost != 0) != 0, 0)) {
+    // a wait gave up: the maximum entering the run from the scores of the
+    // sequence's earlier blocks (all of them whole); the V^ blocks that were in
+    // flight to the two buffers are fetched again
+    AOperand qb[G];                               // (again from LDS: held, they took others' registers)
+    q_operands(qb);
+    h2_t rm[RP];
+#pragma unroll
+    for (int p = 0; p < RP; ++p) rm[p] = h2_t{(half_t)(-__builtin_inff()), (half_t)(-__builtin_inff())};
+    wait_loads<0>();
+    for (int J = 0; J < w.J0; ++J) {
+      load_k(J, 0);
+      wait_loads<0>();
+      float acc[4][RP];
+      score(qb, &sl.buf[0][0], acc);
+#pragma unroll
+      for (int p = 0; p < RP; ++p)
+        rm[p] = hmax2(rm[p], hmax2(scale2_to_f16(acc[0][p], acc[1][p], a.c), scale2_to_f16(acc[2][p], acc[3][p], a.c)));
+    }
+    fetch(nb);
+    if (nb > 1) fetch(nb + 1);
+#pragma unroll
+    for (int p = 0; p < RP; ++p) {
+      m[p] = max_row16(hmax_halves(rm[p]))[0];
+      lost[p] = false;
+    }
   }
 
   // --- softmax, P^ and PV ---
@@ -919,6 +959,7 @@ hipError_t launch_decode(const DecodeLaunch& d, hipStream_t st) {
   a.epoch = next_epoch();
   a.spin_limit = d.test_no_publish ? 16 : kSpinLimit;
   a.publish = d.test_no_publish ? 0 : 1;
+  a.rescore = d.test_no_publish == 1 ? 0 : 1;
   a.o = d.o;
   a.lse = d.lse;
   a.dbg_codes = d.dbg_codes;

@@ -89,3 +89,55 @@ def test_decode_captured_lengths_grow(h, captured, grown, d, hq, hkv):  # noqa: 
         check_close(to_np(got[1][:, live]), to_np(want[1][:, live]), atol=2e-5, rtol=0, what="LSE")
         h.hifa4_decode_fwd(qd, kc, km, vc, vm, cu_seqlens=cu_new, max_seqlen=cap)      # eager work between
         torch.cuda.synchronize()
+
+
+def _case(h, lens, d, hq, hkv, seed):  # noqa: F811
+    _, k, v, cu = small_case(heads_q=hkv, heads_kv=hkv, head_dim=d, seqlens=lens, seed=seed)
+    qd = to_gpu(np.random.default_rng(seed).standard_normal((len(lens), hq, d)).astype(np.float16))
+    return qd, _build_cache(h, k, v, None, cu, max(lens))
+
+
+@pytest.mark.parametrize("lens,d,hq,hkv", [
+    ((700, 65, 64, 1), 128, 8, 2),                   # runs of one block
+    ((4096, 300, 4001), 64, 16, 2),                  # GQA x8
+    ((16384,) * 8, 128, 32, 8),                      # longer runs, the later ones behind 50 others
+    ((16384, 130), 64, 64, 64),
+    ((5000, 2047), 256, 16, 16),
+    ((3000, 129), 256, 40, 8),                       # D = 256, GQA x5
+])
+def test_decode_without_published_maxima(h, lens, d, hq, hkv):  # noqa: F811
+    """No run maximum is published and every wait gives up after 16 polls: each
+    run scores the blocks before it itself, and every output is the same bits."""
+    import torch
+    qd, (kc, km, vc, vm, cu_t) = _case(h, lens, d, hq, hkv, 61)
+    for norm in (h.NORM_PREORDER, h.NORM_INCONSISTENT):
+        kw = dict(cu_seqlens=cu_t, max_seqlen=max(lens), norm=norm)
+        _say("decode without published maxima", lens, d, hq, hkv, norm)
+        for dump in (False, True):
+            want = h.hifa4_decode_fwd(qd, kc, km, vc, vm, debug_p=dump, **kw)
+            got = h.hifa4_decode_fwd(qd, kc, km, vc, vm, debug_p=dump, test_no_publish=2, **kw)
+            torch.cuda.synchronize()
+            assert not torch.isnan(want[0]).any()
+            assert all(torch.equal(a, b) for a, b in zip(got, want)), dump
+
+
+def test_decode_on_two_streams(h):  # noqa: F811
+    """Two calls that each fill the GPU, side by side on two streams with a
+    workspace each: whatever workgroups the one keeps off the GPU while its own
+    wait, both give the bits of a call alone."""
+    import torch
+    cases = [_case(h, (16384,) * 8, 128, 32, 8, 62), _case(h, (9000, 16000, 16384, 300) * 4, 128, 32, 8, 63)]
+    kw = [dict(cu_seqlens=c[1][4], max_seqlen=16384, workspace=h.Workspace()) for c in cases]
+    want = [[x.clone() for x in h.hifa4_decode_fwd(c[0], *c[1][:4], **k)] for c, k in zip(cases, kw)]
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream() for _ in cases]
+    got = [[], []]
+    _say("decode on two streams")
+    for _ in range(20):
+        for i, st in enumerate(streams):
+            with torch.cuda.stream(st):
+                got[i].append(h.hifa4_decode_fwd(cases[i][0], *cases[i][1][:4], **kw[i]))
+    torch.cuda.synchronize()
+    for i in range(2):
+        for o, l in got[i]:
+            assert torch.equal(o, want[i][0]) and torch.equal(l, want[i][1]), i
