@@ -15,6 +15,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import threading
 from dataclasses import dataclass
 from typing import Optional
 
@@ -266,7 +267,9 @@ def hifa4_quantize_v(v, cu_seqlens=None, max_seqlen=None):
 
 
 class Workspace:
-    """A reusable device workspace (grown on demand)."""
+    """A reusable device workspace (grown on demand).  One call at a time may
+    use it: calls on several streams or threads take one each, and a captured
+    call keeps the buffer that it was captured with."""
 
     def __init__(self):
         self.buf = None
@@ -279,7 +282,33 @@ class Workspace:
         return buf
 
 
-_default_ws = Workspace()
+# Workspaces of calls that bring none: one buffer for each stream that a thread
+# uses, since calls of two streams, or of two threads on one stream, may overlap
+# between their launches.  A buffer is allocated on its own stream, so that the
+# memory of one that is replaced or dropped is reused behind the calls that
+# still read it.
+_scratch_buffers = threading.local()
+_MAX_SCRATCH_STREAMS = 16
+
+
+def _capturing() -> bool:
+    return _torch()._C._cuda_isCurrentStreamCapturing()
+
+
+def _scratch(nbytes: int, device, stream: int):
+    bufs = getattr(_scratch_buffers, "by_stream", None)
+    if bufs is None:
+        bufs = _scratch_buffers.by_stream = {}
+    if _capturing():                 # the graph's own memory, not a buffer that may be replaced before a replay
+        return _torch().empty(max(nbytes, 256), dtype=_torch().uint8, device=device)
+    key = (device.index, stream)
+    buf = bufs.get(key)
+    if buf is None or buf.numel() < nbytes:
+        bufs.pop(key, None)
+        while len(bufs) >= _MAX_SCRATCH_STREAMS:
+            del bufs[next(iter(bufs))]
+        buf = bufs[key] = _torch().empty(max(nbytes, 256), dtype=_torch().uint8, device=device)
+    return buf
 
 
 def hifa4_attention_fwd(q, k, v, s=None, cu_seqlens=None, max_seqlen=None, norm: int = NORM_PREORDER,
@@ -318,9 +347,10 @@ def hifa4_attention_fwd(q, k, v, s=None, cu_seqlens=None, max_seqlen=None, norm:
                      0, h0, nh, t0, nt)
     p = sh.problem()
     need = int(lib.hifa4_workspace_bytes(ctypes.byref(p), ctypes.byref(opt)))
-    ws = (workspace or _default_ws).get(need, dev)
+    stream = _stream(dev)
+    ws = _scratch(need, dev, stream) if workspace is None else workspace.get(need, dev)
     _check(lib.hifa4_attention_fwd(ctypes.byref(p), ctypes.byref(opt), _ptr(q), _ptr(k), _ptr(v), _ptr(s),
-                                   _ptr(o), _ptr(l), _ptr(ws), ws.numel(), _stream(dev)), "hifa4_attention_fwd")
+                                   _ptr(o), _ptr(l), _ptr(ws), ws.numel(), stream), "hifa4_attention_fwd")
     if debug_p:
         return o, l, pc, pm
     return o, l
@@ -417,10 +447,11 @@ def hifa4_decode_fwd(q, k_codes, k_meta, v_codes, v_meta, s=None, cu_seqlens=Non
                      int(test_no_publish))
     p = sh.problem()
     need = int(lib.hifa4_decode_workspace_bytes(ctypes.byref(p)))
-    ws = (workspace or _default_ws).get(need, dev)
+    stream = _stream(dev)
+    ws = _scratch(need, dev, stream) if workspace is None else workspace.get(need, dev)
     _check(lib.hifa4_decode_fwd(ctypes.byref(p), ctypes.byref(opt), _ptr(q), _ptr(k_codes), _ptr(k_meta),
                                 _ptr(v_codes), _ptr(v_meta), _ptr(s), _ptr(o), _ptr(l), _ptr(ws), ws.numel(),
-                                _stream(dev)), "hifa4_decode_fwd")
+                                stream), "hifa4_decode_fwd")
     if debug_p:
         return o, l, pc, pm
     return o, l
