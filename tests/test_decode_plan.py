@@ -24,16 +24,20 @@ extern "C" size_t need(int batch, int hq, int d, long runs, long words, int pack
 """
 
 
-@pytest.fixture(scope="module")
-def host(tmp_path_factory):
-    if not have_compiler():
-        pytest.skip("g++ not available")
-    lib = compile_host(SOURCE, tmp_path_factory.mktemp("plan"))
+def load_plan(folder):
+    lib = compile_host(SOURCE, folder)
     i, n = ctypes.c_int, ctypes.c_long
     lib.plan.argtypes, lib.plan.restype = [i, i, i, i, i, n, ctypes.POINTER(n)], None
     lib.room.argtypes, lib.room.restype = [i] * 5, ctypes.c_size_t
     lib.need.argtypes, lib.need.restype = [i, i, i, n, n, i], ctypes.c_size_t
     return lib
+
+
+@pytest.fixture(scope="module")
+def host(tmp_path_factory):
+    if not have_compiler():
+        pytest.skip("g++ not available")
+    return load_plan(tmp_path_factory.mktemp("plan"))
 
 
 def plan(host, batch, hq, hkv, d, nb, tokens):

@@ -62,7 +62,11 @@ def _decode_and_compare(h, qd, k, v, cu, s, max_seqlen, norm="preorder", seqs=No
     nm = h.NORM_PREORDER if norm == "preorder" else h.NORM_INCONSISTENT
     o, lse, pc, pm = h.hifa4_decode_fwd(to_gpu(qd), kc, km, vc, vm, None if s is None else to_gpu(s),
                                         cu_seqlens=cu_t, max_seqlen=max_seqlen, norm=nm, debug_p=True)
+    # the kernel of calls without the dump is another one: the same bits
+    o_n, lse_n = h.hifa4_decode_fwd(to_gpu(qd), kc, km, vc, vm, None if s is None else to_gpu(s),
+                                    cu_seqlens=cu_t, max_seqlen=max_seqlen, norm=nm)
     o, lse, pc, pm = to_np(o), to_np(lse), to_np(pc), to_np(pm).view(np.uint32)
+    o_n, lse_n = to_np(o_n), to_np(lse_n)
     worst = 0.0
     for b in (range(b_all) if seqs is None else seqs):
         if cu is None:
@@ -72,6 +76,8 @@ def _decode_and_compare(h, qd, k, v, cu, s, max_seqlen, norm="preorder", seqs=No
         L = k_seq.shape[0]
         if L == 0:
             continue                                # an empty sequence has no decode row
+        assert np.array_equal(o[b].view(np.uint16), o_n[b].view(np.uint16)), f"O without the dump, seq {b}"
+        assert np.array_equal(lse[:, b].view(np.uint32), lse_n[:, b].view(np.uint32)), f"LSE without the dump, seq {b}"
         nb = -(-L // 64)
         for hk in (range(hkv) if kv_heads is None else kv_heads):
             for j, r in enumerate(_oracle_row(qd[b], k_seq, v_seq, s, hk, grp, norm)):
@@ -130,14 +136,13 @@ def test_decode_fixed_length(h):
 
 
 @pytest.mark.parametrize("lens,d,hq,hkv,seed", [
-    ((5000,), 128, 4, 1, 5),          # 79 blocks: score runs of 1, 40 splits of 2
-    ((19000,), 128, 4, 1, 12),        # 297 blocks: 75 splits of 4
-    ((33000,), 64, 2, 1, 6),          # 516 blocks: 65 splits of 8 (two 64-split passes of the merge)
-    ((16384, 16384), 64, 16, 16, 13), # two workgroups of kv heads: score runs of 2, 64 splits of 4
+    ((5000,), 128, 4, 1, 5),          # 79 blocks: 40 runs of 2
+    ((19000,), 128, 4, 1, 12),        # 297 blocks: 99 runs of 3 (two 64-run passes of the merge)
+    ((33000,), 64, 2, 1, 6),          # 516 blocks: 104 runs of 5
+    ((16384, 16384), 64, 16, 16, 13), # four workgroups of kv heads: 52 runs of 5 each
 ])
 def test_decode_many_splits(h, lens, d, hq, hkv, seed):
-    """Long sequences, one shape per score-run and split length the launch
-    picks from the block count, batch and kv heads."""
+    """Long sequences of many runs."""
     q, k, v, cu = small_case(heads_q=hq, heads_kv=hkv, head_dim=d, seqlens=lens, seed=seed)
     s = np.exp(np.random.default_rng(seed).uniform(-1, 1, (hkv, d))).astype(np.float32)
     _say("decode long", lens, d, hq, hkv)
@@ -145,18 +150,17 @@ def test_decode_many_splits(h, lens, d, hq, hkv, seed):
 
 
 @pytest.mark.parametrize("lens,d,hq,hkv,seed,seqs,kv_heads", [
-    # 64 kv heads in 8 workgroups, 58 blocks: runs and splits of 8, GQA x1
+    # 64 kv heads in 8 workgroups, 58 blocks: runs of 8, GQA x1
     ((3648, 3600, 3700, 3500, 3648, 3100, 3648, 3648), 64, 64, 64, 15, [0, 2, 5], [0, 37, 63]),
     # GQA x8 (two rows per softmax lane pass), 256 blocks in 2 workgroups of kv heads
     ((16384, 16000, 16384, 15000, 16384, 16300, 16384, 9000), 64, 128, 16, 16, [1, 7], [0, 9, 15]),
-    # 64 blocks: runs and splits of 2, GQA x4, D=128
+    # 64 blocks: runs of 2, GQA x4, D=128
     ((4096, 4000, 4096, 3900, 4096, 4033, 4096, 2000), 128, 8, 2, 17, [0, 3, 7], [0, 1]),
 ])
 def test_decode_fused_runs(h, lens, d, hq, hkv, seed, seqs, kv_heads):
-    """Shapes whose splits fill the chip, so one kernel computes the scores
-    of a split's blocks into LDS, publishes each row's run maximum and reads
-    the earlier runs' maxima of its sequence: every P^ code of the sampled
-    rows bit-exact."""
+    """Shapes of many workgroups, whose runs wait for the maxima that earlier
+    runs of their sequence publish: every P^ code of the sampled rows
+    bit-exact."""
     _, k, v, cu = small_case(heads_q=hkv, heads_kv=hkv, head_dim=d, seqlens=lens, seed=seed)
     qd = np.random.default_rng(seed).standard_normal((len(lens), hq, d)).astype(np.float16)
     s = np.exp(np.random.default_rng(seed).uniform(-1, 1, (hkv, d))).astype(np.float32)
@@ -269,8 +273,7 @@ def test_decode_graph_replay(h):
 
 def _fused_case():
     """8 sequences of about 4096 tokens, 2 kv heads, GQA x4, D=128: 64 blocks
-    per row in splits of 2, 256 split workgroups, so scores and splits run in
-    one kernel that waits on run maxima."""
+    per row in runs of 2 that wait on run maxima."""
     lens = (4096, 4000, 4096, 3900, 4096, 4033, 4096, 2000)
     _, k, v, cu = small_case(heads_q=2, heads_kv=2, head_dim=128, seqlens=lens, seed=31)
     s = np.exp(np.random.default_rng(31).uniform(-1, 1, (2, 128))).astype(np.float32)
@@ -278,11 +281,11 @@ def _fused_case():
 
 
 def test_decode_graph_replay_fused(h):
-    """The fused decode step captured once and replayed back to back with a
+    """The decode step captured once and replayed back to back with a
     new query written in place before each replay (no eager decode call in
     between): every replay equals an eager call on the same query bit for
     bit, and its P^ codes equal the oracle's on sampled rows.  A replay reuses
-    the captured call's tag, so this fails if a split can take the previous
+    the captured call's tag, so this fails if a run can take the previous
     replay's run maxima for its own."""
     import torch
     lens, k, v, cu, s = _fused_case()
@@ -328,9 +331,9 @@ def test_decode_graph_replay_fused(h):
 
 
 def test_decode_wait_gives_up(h):
-    """The bounded wait of the fused kernel made to give up from the host (no
-    run maxima published, 16 polls per wait): every kernel ends and each row,
-    whose later splits all lost their wait, comes out NaN rather than
+    """The bounded wait made to give up from the host (no run maxima published,
+    16 polls per wait) with no run making up for it: every kernel ends and each
+    row, whose later runs all lost their wait, comes out NaN rather than
     silently wrong; the next normal call is correct again."""
     import torch
     lens, k, v, cu, s = _fused_case()
@@ -346,15 +349,15 @@ def test_decode_wait_gives_up(h):
 
 
 @pytest.mark.parametrize("kind,jump_block,lens", [
-    ("wipe", 2, (450, 200)),          # the jump opens the second split: the merge wipes the first
-    ("wipe", 1, (450, 200)),          # the jump inside the first split
+    ("wipe", 2, (450, 200)),          # runs of 2: the jump opens the second, the merge wipes the first
+    ("wipe", 1, (450, 200)),          # the jump inside the first run
     ("renorm", 0, (450, 400)),
-    ("wipe", 2, (4096,) * 8),         # fused shape (256 split workgroups)
+    ("wipe", 2, (4096,) * 8),         # runs of 3, 176 workgroups
     ("renorm", 0, (4096,) * 8),
 ])
 def test_decode_running_max_special_paths(h, kind, jump_block, lens):
     """The decode row (L-1) of inputs whose running maximum jumps by more
-    than 25 log2 units (a rescale factor of 0, so earlier blocks or splits
+    than 25 log2 units (a rescale factor of 0, so earlier blocks or runs
     are wiped) or rises over 64 units in smaller steps: every P^ code of the
     sampled rows bit-exact, O and LSE, both normalizers."""
     from _jump import check_jumps, jump_case

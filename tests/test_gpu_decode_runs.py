@@ -1,15 +1,18 @@
 """Decode step: every way a call's blocks become runs.  Run lengths of 1 to 8
-blocks, odd and even, runs numbered over the sequences' own lengths (up to 256
-sequences, the prefix sum over the batch in one to four steps) or over the
-longest one (more sequences, or no cu_seqlens), last blocks of 1 to 64 keys,
-empty sequences, four and eight waves per workgroup.  Every P^ code of the
-sampled rows bit-exact against the oracle, O and LSE within the parity bar."""
+blocks, numbered over the sequences' own lengths (up to 256 sequences, the
+prefix sum over the batch in one to four steps) or over the longest one (more
+sequences, or no cu_seqlens), last blocks of 1 to 64 keys, empty sequences, one
+to eight waves per workgroup; each case asserts the plan that it stands for.
+Every P^ code of the sampled rows bit-exact against the oracle, O and LSE
+within the parity bar and the same bits without the P^ dump.  Then lengths that
+grow under a captured call, waits that give up, and calls on two streams."""
 import numpy as np
 import pytest
 
 from paper_2607_04302_amd.workloads import small_case
 
 from _gpu_util import check_close, to_gpu, to_np
+from test_decode_plan import load_plan, plan
 from test_gpu_decode import _build_cache, _decode_and_compare, _say, h  # noqa: F401  (h: the library fixture)
 
 pytestmark = pytest.mark.gpu
@@ -21,22 +24,51 @@ def _lens(n, lo, hi, seed, empty=()):
     return tuple(int(v) for v in x)
 
 
-@pytest.mark.parametrize("lens,d,hq,hkv,seqs,kv_heads", [
-    ((64, 65, 127, 128, 1, 63), 128, 8, 2, None, None),                  # runs of 1, every kind of last block
-    (_lens(70, 1, 200, 1, empty=(0, 63, 64)), 64, 2, 1, [1, 62, 65, 69], None),     # two steps of the prefix sum
-    (_lens(200, 1, 90, 2, empty=(199,)), 128, 4, 1, [0, 127, 128, 198], None),       # four steps
-    (_lens(300, 1, 150, 3, empty=(5, 299)), 64, 1, 1, [0, 4, 256, 298], None),       # above 256 sequences
-    ((2999, 3300, 70, 3265), 64, 64, 64, [0, 2, 3], [0, 63]),            # runs of 3
-    ((4001, 4100, 3900, 4096, 64), 64, 64, 64, [1, 4], [5]),             # runs of 5
-    ((5000, 4097, 63), 256, 16, 16, [0, 1, 2], [0, 15]),                 # D = 256: four waves, runs of 2
-    ((3000, 2047), 256, 40, 8, [0, 1], [7]),                             # two rows per lane, GQA x5
+@pytest.fixture(scope="module")
+def planner(tmp_path_factory):
+    lib = load_plan(tmp_path_factory.mktemp("plan"))
+
+    def of(lens, max_seqlen, d, hq, hkv, cu=True):
+        p = plan(lib, len(lens), hq, hkv, d, -(-max_seqlen // 64), sum(lens) if cu else -1)
+        return p["bps"], p["packed"], p["waves"]
+    return of
+
+
+# want: blocks per run, runs numbered over the own lengths, waves per workgroup
+@pytest.mark.parametrize("lens,d,hq,hkv,seqs,kv_heads,want", [
+    ((64, 65, 127, 128, 1, 63), 128, 8, 2, None, None, (2, 1, 1)),                  # every kind of last block
+    (_lens(70, 1, 200, 1, empty=(0, 63, 64)), 64, 2, 1, [1, 62, 65, 69], None, (1, 1, 1)),     # two prefix-sum steps
+    (_lens(200, 1, 90, 2, empty=(199,)), 128, 4, 1, [0, 127, 128, 198], None, (2, 1, 1)),      # four steps
+    (_lens(300, 1, 150, 3, empty=(5, 299)), 64, 1, 1, [0, 4, 256, 298], None, (3, 0, 1)),      # above 256 sequences
+    ((2999, 3300, 70, 3265), 64, 64, 64, [0, 2, 3], [0, 63], (4, 1, 8)),
+    ((4001, 4100, 3900, 4096, 64), 64, 64, 64, [1, 4], [5], (7, 1, 8)),
+    ((5000, 4097, 63), 256, 16, 16, [0, 1, 2], [0, 15], (2, 1, 4)),                 # D = 256
+    ((3000, 2047), 256, 40, 8, [0, 1], [7], (2, 1, 1)),                             # two rows per lane, GQA x5
 ])
-def test_decode_run_shapes(h, lens, d, hq, hkv, seqs, kv_heads):  # noqa: F811
+def test_decode_run_shapes(h, planner, lens, d, hq, hkv, seqs, kv_heads, want):  # noqa: F811
+    assert planner(lens, max(lens), d, hq, hkv) == want
     _, k, v, cu = small_case(heads_q=hkv, heads_kv=hkv, head_dim=d, seqlens=lens, seed=41)
     qd = np.random.default_rng(42).standard_normal((len(lens), hq, d)).astype(np.float16)
     s = np.exp(np.random.default_rng(43).uniform(-1, 1, (hkv, d))).astype(np.float32)
     _say("decode runs", len(lens), max(lens), d, hq, hkv)
     _decode_and_compare(h, qd, k, v, cu, s, max(lens), seqs=seqs, kv_heads=kv_heads)
+
+
+@pytest.mark.parametrize("blocks,d,hq", [(1, 128, 4), (2, 64, 8), (3, 256, 1), (4, 128, 8), (5, 64, 2), (6, 256, 2),
+                                         (7, 128, 1), (8, 64, 4)])
+def test_decode_run_lengths(h, planner, blocks, d, hq):  # noqa: F811
+    """Every run length, by the longest sequence (128 runs of it): in calls of
+    two packed sequences, and of one sequence without cu_seqlens (its runs of
+    one block are those of one block in all)."""
+    lens = (8192 * blocks - 3, 130)
+    assert planner(lens, lens[0], d, hq, 1)[:2] == (blocks, 1)
+    _, k, v, cu = small_case(heads_q=1, heads_kv=1, head_dim=d, seqlens=lens, seed=46)
+    qd = np.random.default_rng(47).standard_normal((2, hq, d)).astype(np.float16)
+    _say("decode run lengths", blocks, d, hq)
+    _decode_and_compare(h, qd, k, v, cu, None, lens[0])
+    n = lens[0] if blocks > 1 else 60
+    assert planner((n,), n, d, hq, 1, cu=False)[:2] == (blocks, 0)
+    _decode_and_compare(h, qd[:1], k[None, :n], v[None, :n], None, None, n)
 
 
 @pytest.mark.parametrize("norm", ["preorder", "inconsistent"])
@@ -51,10 +83,10 @@ def test_decode_max_seqlen_above_every_length(h, norm):  # noqa: F811
 
 
 @pytest.mark.parametrize("captured,grown,d,hq,hkv", [
-    ((64, 1, 30), (1500, 64, 2000), 128, 8, 2),              # runs of 1 or 2, several per workgroup
-    ((1, 1), (9000, 8191), 64, 8, 8),                        # runs lengthened until they fit the workspace
-    ((200,) * 70, (700,) * 35 + (65,) * 35, 64, 2, 1),       # two steps of the prefix sum
-    ((5, 0, 3), (300, 1200, 0), 256, 8, 1),                  # two rows per lane; a sequence appears, another empties
+    ((64, 1, 30), (1500, 64, 2000), 128, 8, 2),              # planned runs of 1 become 6, several per workgroup
+    ((1, 1), (9000, 8191), 64, 8, 8),                        # 2 become 8, 34 runs in 2 workgroups
+    ((200,) * 70, (700,) * 35 + (65,) * 35, 64, 2, 1),       # 1 become 4, two steps of the prefix sum
+    ((5, 0, 3), (300, 1200, 0), 256, 8, 1),                  # 1 become 3; a sequence appears, another empties
 ])
 def test_decode_captured_lengths_grow(h, captured, grown, d, hq, hkv):  # noqa: F811
     """A captured step replayed over lengths that have grown in place past the
