@@ -296,10 +296,13 @@ def _capturing() -> bool:
 
 
 def _scratch(nbytes: int, device, stream: int):
-    bufs = getattr(_scratch_buffers, "by_stream", None)
-    if bufs is None:
+    try:
+        bufs = _scratch_buffers.by_stream
+    except AttributeError:
         bufs = _scratch_buffers.by_stream = {}
-    if _capturing():                 # the graph's own memory, not a buffer that may be replaced before a replay
+    # captured: the graph's own memory, not a buffer that may be replaced before
+    # a replay (the default stream, handle 0, cannot be captured)
+    if stream and _capturing():
         return _torch().empty(max(nbytes, 256), dtype=_torch().uint8, device=device)
     key = (device.index, stream)
     buf = bufs.get(key)
