@@ -42,11 +42,13 @@
 //
 // What bounds it: one step of 8 sequences of 32768 tokens (Hq 32, Hkv 8, D 128)
 // reads 302 MB, 59 us at the 5.1 TB/s that large reads reach on this card, and
-// takes 77 us (89 us before); 32 sequences of 300 to 8192 tokens take 50.5 us
-// (82.5), one of 4096 tokens 15 us (20.6; its kernels 13.9).  Until now codes became int8
-// operands, 9400 VALU instructions a wave for 8 blocks (512 of them
-// quarter-rate multiplies) against 4750 here; the VALU is now busy half of the
-// time and the cache streams at 4.3 TB/s beside it.
+// takes 77 us where several such caches take turns (72 us over one, part of
+// which the 256 MB cache beside the memory holds); 32 sequences of 300 to 8192
+// tokens take 50 us, one of 4096 tokens 15 us (12.4 into outputs that the caller brings).  The VALU is
+// busy half of the time and the cache streams at 4.3 TB/s beside it.  With the
+// codes turned into int8 operands (9400 VALU instructions a wave for 8 blocks,
+// 512 of them quarter-rate multiplies, against 4750 here) the three took 89,
+// 82.5 and 20.6 us.
 //
 // MFMA operand convention: lane l holds row / column n = l & 15 of A / B and
 // the K slots 32q..32q+31, q = l >> 4; output value i of lane l is row 4q + i,
@@ -268,7 +270,7 @@ struct Stage {
 // Asynchronous copies of 64 lanes x 16 or 4 bytes straight into LDS: lane i
 // reads at base + off and its bytes land at m0 + 16 i (4 i).  Written out with
 // a scalar base; completion is counted in vmcnt, in issue order.  Nothing else
-// in this file may use M0 (tests/test_m0_guard.py).
+// in this file may use M0 (tests/test_m0_guard_decode.py).
 __device__ __forceinline__ void dma16(const uint8_t* base, uint32_t off, uint32_t m0) {
   asm volatile("s_mov_b32 m0, %2\n\tglobal_load_lds_dwordx4 %0, %1" : : "v"(off), "s"(base), "s"(m0) : "memory", "m0");
 }

@@ -36,7 +36,9 @@ inline size_t pad256(size_t x) { return (x + 255) & ~(size_t)255; }
 // 64) alone: n splits of 8, 4 or 2 blocks per row (the longest that gives 256
 // workgroups of eight kv heads, at most 128 per row), for each a partial O, l,
 // factor product and maximum, and 8 bytes per split where those splits fill
-// the chip, else the room of a row's fp16 scores and block maxima.
+// the chip, else the room of a row's fp16 scores and block maxima.  The kernels
+// below keep neither scores nor that run length; the size stays what callers
+// have always been told, and the plan fits its runs into it.
 inline size_t decode_workspace_bytes(int batch, int hq, int hkv, int D, int NB) {
   const long groups = (long)batch * ((hkv + 7) / 8);
   size_t n = ((size_t)NB + 7) / 8;
@@ -51,14 +53,20 @@ inline size_t decode_workspace_bytes(int batch, int hq, int hkv, int D, int NB) 
   return b + pad256(rows * NB * 128) + pad256(rows * ((NB + 7) & ~7) * 2);
 }
 
-// Run length, workgroup shape and grid of a call.  The longest useful run is
-// the one with which every wave of the call is resident at once (one round of
-// waves, 16 or 8 per compute unit as the registers and the LDS allow); shorter
-// runs would only add partial outputs, longer ones leave the chip idle.  At
-// least ceil(NB/128) blocks, since every split of a row adds to its look-back
-// and merge, and at most 8, which is what the registers of a wave hold; and as
-// many as it takes for the partials to fit the workspace.  The workgroup takes
-// fewer waves where eight per workgroup would leave compute units empty.
+// Run length, workgroup shape and grid of a call.  Aimed at is one round of
+// waves: the run with which all waves of the call make 16 (or 8, as the
+// registers allow) per compute unit; shorter runs would only add partial
+// outputs, longer ones leave the chip idle.  At least ceil(NB/128) blocks, since
+// every run of a row adds to its look-back and merge, and at most 8, which is
+// what the registers of a wave hold; and as many as it takes for the partials to
+// fit the workspace, which lengthens the runs of 4 to 7 sequences of 32768
+// tokens to 8 (half a round at 4).  A workgroup's LDS is that of eight waves
+// (four at D = 256) whatever it launches, so with few kv heads fewer waves are
+// resident than aimed at: at D = 128 two of a compute unit with one kv head,
+// four with two.  The workgroup takes fewer waves where eight per workgroup
+// would leave compute units empty.  Measured at D = 128 with four query heads per
+// kv head: one sequence of 8192, 32768 and 131072 tokens of 8 kv heads 14, 21 and
+// 41 us; four of 32768 tokens 37 us, with 1, 2 and 4 kv heads 23, 25 and 27 us.
 struct DecodePlan {
   int waves, bps, packed;
   long runs;               // runs of the grid

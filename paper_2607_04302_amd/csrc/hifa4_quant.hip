@@ -615,10 +615,10 @@ __global__ void __launch_bounds__(kCalibThreads) k_calib(CalibArgs a) {
 // and alpha in place of the first bins.  The formulas are evaluated step by
 // step (no contraction into fused multiply-adds).
 //
-// Both kernels replace a copy of the statistics to the host and the same sums
-// there: 390 KB through pageable memory, three passes over the bins and two
-// pow() per channel: 273 us a call before, 191 us with it (16 x 4096 tokens, 32 + 8
-// heads, D = 128), of which the pass over Q and K takes 145 us.
+// On the GPU and not on the host, where the same sums need a copy of 390 KB
+// through pageable memory, three passes over the bins and two pow() per
+// channel: 16 x 4096 tokens of 32 + 8 heads, D = 128, take 193 us a call against
+// 273, of which the pass over Q and K is 145 us.
 constexpr int kGateThreads = 1024;
 
 __global__ void __launch_bounds__(kGateThreads) k_calib_gate(const uint32_t* __restrict__ stats,
